@@ -7,8 +7,10 @@
 // trials.
 //
 // This file is compiled at plan time. The generated prologue fixes the store
-// dtype (ST), the number of widths (NSFRB_NW) and the shape classes; the
-// generated boxcar plan (nsfrb_chain) follows this file. DM trials, delays,
+// dtype (ST), the number of widths (NSFRB_NW), the shape classes and the samples
+// per lane C of each length class LC (lane_samples: where rows are read in
+// pairs C is even, at most three more than LC); the generated boxcar plan
+// (nsfrb_chain) follows this file. DM trials, delays,
 // n_sub and n_t stay runtime values.
 //
 // Layout and work split (gfx950, wave64):
@@ -18,12 +20,13 @@
 //    past the end of a de-dispersed series sums to -inf and is never a maximum;
 //  * NW/PIX waves share a pixel and split its DM trials round-robin (the
 //    "DM chunk" of a wave is every (NW/PIX)-th trial);
-//  * lane l holds the C consecutive samples t = C*l + c (FP32 rows: C odd, so
-//    lanes hit distinct LDS banks at any delay; FP16 rows: C even with C/2
-//    odd, read as dwords holding two samples);
+//  * lane l holds the C consecutive samples t = C*l + c (C odd, one sample per
+//    read, or C even with C/2 odd, read in pairs: either way lanes hit distinct
+//    LDS banks at any delay);
 //  * D_d[t] = sum_s z[s][t + delta[d][s]] is formed in registers (FP32); an
 //    FP16 sample is added by v_fma_mix_f32 (f16 operand * 1.0 + f32), one
-//    rounding, the same result as converting and then adding;
+//    rounding, the same result as converting and then adding; a BF16 sample
+//    is the upper half of the FP32 it stands for;
 //  * boxcars use the pairwise doubling B_2w[t] = B_w[t] + B_w[t+w]; a width
 //    that is not a power of two is the sum of the power-of-two windows of its
 //    binary digits placed end to end. Each output is a balanced sum, so the
@@ -92,46 +95,135 @@ __device__ __forceinline__ void copy_arr(float (&out)[C], const float (&a)[C]) {
   for (int c = 0; c < C; ++c) out[c] = a[c];
 }
 
-// acc + (FP16 sample in the low / high half of w), rounded once.
-__device__ __forceinline__ float add_f16_lo(float acc, uint32_t w) {
-  float r;
-  asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(acc));
-  return r;
-}
-__device__ __forceinline__ float add_f16_hi(float acc, uint32_t w) {
-  float r;
-  asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(acc));
-  return r;
-}
+// De-dispersion: cur[c] += row_s[delay_s + C * lane + c] for c < C, sub-band by
+// sub-band. Reads are grouped ahead of the adds that use them: left to itself
+// the compiler reused one register pair for a whole row, so each pair of
+// samples waited out its own LDS round trip (17 in a row of 33 samples).
+//
+// RowPart: the samples [C0, C0 + N) of a lane's C samples of one row, read into
+// registers by load() and added by add(). Odd C: one sample per read; lanes C
+// apart hit distinct banks. PAIRED (even C with C/2 odd, C0 and N even): two
+// samples per read, which the LDS delivers at twice the rate (FP32: 220 against
+// 116 bytes per clock and CU) but only from aligned addresses. The lane's
+// samples start at element e0 = dl + C*l, whose parity is that of dl (uniform);
+// pair k holds elements (2k, 2k+1) counted from e0 rounded down to even. With
+// odd dl the samples straddle one element of the next pair; with even dl that
+// read repeats the last one.
+template <typename T, int N, bool PAIRED>
+struct RowPart {
+  float v[N];
+  template <int C, int C0>
+  __device__ __forceinline__ void load(const T* row, int dl, int l) {
+    const T* r = row + dl + C * l + C0;
+#pragma unroll
+    for (int c = 0; c < N; ++c) v[c] = to_f32(r[c]);
+  }
+  __device__ __forceinline__ void add(float* cur, int) const {
+#pragma unroll
+    for (int c = 0; c < N; ++c) cur[c] += v[c];
+  }
+  template <class Next>
+  __device__ __forceinline__ void add(float* cur, int dl, const Next&) const {
+    add(cur, dl);
+  }
+};
+// cur[i] += sample i of N read in pairs, for either parity of dl (generated with
+// the plan: the two cases are branches inside one asm block, since as C++
+// branches the compiler merges them into adds whose operands it copies or
+// selects first).
+template <int N>
+__device__ __forceinline__ void add_pairs(float* cur, const float2* w, float end, int dl);
+template <int N>
+__device__ __forceinline__ void add_pairs(float* cur, const uint32_t* w, _Float16, int dl);   // N/2 + 1 dwords
+template <int N>
+__device__ __forceinline__ void add_pairs(float* cur, const uint32_t* w, bf16_t, int dl);
+template <int N>
+struct RowPart<float, N, true> {
+  static_assert((N & 1) == 0, "paired rows are read two samples at a time");
+  float2 w[N / 2];
+  float end;
+  template <int C, int C0>
+  __device__ __forceinline__ void load(const float* row, int dl, int l) {
+    // (the first part of a row takes the sample after its own from the second)
+    static_assert((C & 1) == 0 && (C0 & 1) == 0, "paired rows need an even number of samples per lane");
+    const float2* r = reinterpret_cast<const float2*>(row) + ((dl + C * l) >> 1) + C0 / 2;
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) {
+      w[k] = r[k];
+      asm volatile("" ::: "memory");     // ds_read2_b64, which two reads would become, has half ds_read_b64's rate
+    }
+    if (C0 + N == C) end = reinterpret_cast<const float*>(r)[N - 1 + (dl & 1)];
+  }
+  template <class Next>
+  __device__ __forceinline__ void add(float* cur, int dl, const Next& next) {
+    end = next.w[0].x;
+    add(cur, dl);
+  }
+  __device__ __forceinline__ void add(float* cur, int dl) const { add_pairs<N>(cur, w, end, dl); }
+};
+template <typename T, int N>
+struct RowPart<T, N, true> {
+  static_assert((N & 1) == 0, "paired rows are read two samples at a time");
+  uint32_t w[N / 2 + 1];
+  template <int C, int C0>
+  __device__ __forceinline__ void load(const T* row, int dl, int l) {
+    static_assert((C & 1) == 0 && (C0 & 1) == 0, "paired rows need an even number of samples per lane");
+    const uint32_t* r = reinterpret_cast<const uint32_t*>(row) + ((dl + C * l) >> 1) + C0 / 2;
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) w[k] = r[k];
+    if (C0 + N == C) w[N / 2] = r[N / 2 - 1 + (dl & 1)];
+  }
+  template <class Next>
+  __device__ __forceinline__ void add(float* cur, int dl, const Next& next) {
+    w[N / 2] = next.w[0];
+    add(cur, dl);
+  }
+  __device__ __forceinline__ void add(float* cur, int dl) const { add_pairs<N>(cur, w, T(), dl); }
+};
 
-// cur[c] += row[e0 + c] for c < C, e0 = delay + C * lane.
-template <int C, typename T>
-__device__ __forceinline__ void add_row(float (&cur)[C], const T* row, int dl, int l) {
-  const T* r = row + dl + C * l;
+// Nothing is scheduled across: the reads above stay ahead of the adds below.
+__device__ __forceinline__ void reads_first() { __builtin_amdgcn_sched_barrier(0); }
+
+// The de-dispersed series of one trial in cur. delay(s): sub-band s's delay, a
+// uniform value. Series of kSplitC samples per lane or more are read in
+// two half rows, the other half in flight while one is added. Shorter ones run
+// with enough waves to hide the read latency, and lose more by the registers
+// (waves) the second half costs (7 samples per lane: 517 against 582 us for a
+// 5x-binned survey quarter), as do lean plans (NSFRB_LEAN: the tuned one would
+// spill); they leave the order of reads and adds to the compiler.
+constexpr int kSplitC = 20;
+constexpr bool split_rows(int C) { return C >= kSplitC && !NSFRB_LEAN; }
+template <int C, typename T, class Delay>
+__device__ __forceinline__ void dedisperse(float (&cur)[C], const T* rows, int rs, int n_sub, const Delay& delay, int l) {
 #pragma unroll
-  for (int c = 0; c < C; ++c) cur[c] += to_f32(r[c]);
-}
-// FP16 rows (row start dword-aligned, C even): the samples of a lane start at
-// element e0 = dl + C*l, whose parity is that of dl (uniform); dword k of the
-// lane holds elements (2k, 2k+1) counted from e0 rounded down to even.
-template <int C>
-__device__ __forceinline__ void add_row(float (&cur)[C], const _Float16* row, int dl, int l) {
-  static_assert((C & 1) == 0, "FP16 rows need an even number of samples per lane");
-  const uint32_t* w = reinterpret_cast<const uint32_t*>(row) + ((dl + C * l) >> 1);
-  if (dl & 1) {
-    cur[0] = add_f16_hi(cur[0], w[0]);
-#pragma unroll
-    for (int k = 0; k < C / 2; ++k) {
-      const uint32_t v = w[k + 1];
-      cur[2 * k + 1] = add_f16_lo(cur[2 * k + 1], v);
-      if (2 * k + 2 < C) cur[2 * k + 2] = add_f16_hi(cur[2 * k + 2], v);
+  for (int c = 0; c < C; ++c) cur[c] = 0.f;
+  constexpr bool paired = (C & 1) == 0;
+  if constexpr (!split_rows(C)) {
+    for (int s = 0; s < n_sub; ++s) {
+      const int dl = delay(s);
+      RowPart<T, C, paired> a;
+      a.template load<C, 0>(rows + s * rs, dl, l);
+      a.add(cur, dl);
     }
   } else {
-#pragma unroll
-    for (int k = 0; k < C / 2; ++k) {
-      const uint32_t v = w[k];
-      cur[2 * k] = add_f16_lo(cur[2 * k], v);
-      cur[2 * k + 1] = add_f16_hi(cur[2 * k + 1], v);
+    constexpr int H = (C / 2 + 1) & ~1;                  // even, about half a row
+    RowPart<T, H, paired> a;
+    RowPart<T, C - H, paired> b;
+    int dl = delay(0);
+    a.template load<C, 0>(rows, dl, l);
+    for (int s = 0; s < n_sub; ++s) {
+      b.template load<C, H>(rows + s * rs, dl, l);
+      reads_first();
+      a.add(cur, dl, b);
+      // (the last row's first half is read once more: a branch around the reads
+      // would make the compiler copy the registers)
+      const int sn = s + 1 < n_sub ? s + 1 : s;
+      const int dn = delay(sn);
+      reads_first();
+      a.template load<C, 0>(rows + sn * rs, dn, l);
+      reads_first();
+      b.add(cur + H, dl);
+      dl = dn;
     }
   }
 }
@@ -148,11 +240,49 @@ __device__ __forceinline__ bool better(float s, int d, int w, const Best& b) {
   return (s > b.s) | ((s == b.s) & ((d < b.d) | ((d == b.d) & (w < b.w))));
 }
 
+// Maximum over the wave, as a scalar: the 16 lanes of each row by DPP, then row
+// to row by broadcasts of a row's last lane, so that lane 63 ends with the
+// whole wave's. Six instructions and a lane read, with the wait states that a
+// written register needs: two before a DPP operand, one before a lane read and,
+// for the scalar it writes, two before a vector instruction. The compiler's
+// form of the same moves takes a separate move for each step.
+__device__ __forceinline__ float wave_max_uniform(float v) {
+  float t, r;
+  asm volatile("s_nop 1\n\t"
+      "v_max_f32_dpp %0, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+      "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+      "v_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+      "v_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+      "v_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\ts_nop 1\n\t"
+      "v_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\ts_nop 0\n\t"
+      "v_readlane_b32 %1, %0, 63\n\ts_nop 1"
+      : "=&v"(t), "=s"(r) : "v"(v));
+  return r;
+}
+
+// First register c with b[c] == M in lane L, by one compare per register
+// (compares write lane masks to scalar registers; lane L's bit is tested on the
+// scalar unit). For longer series the plan generates a specialisation that
+// looks for the group of registers first.
+template <int C>
+__device__ __forceinline__ int locate_first(const float (&b)[C], float M, int L) {
+  int cf = C - 1;
+#pragma unroll
+  for (int c = C - 2; c >= 0; --c) {
+    // cf = c if lane L's bit of the compare mask is set: s_bitcmp1_b64 tests
+    // the bit straight into SCC (two scalar instructions per register; the
+    // compiler's mask-and-compare form takes three)
+    const uint64_t mk = ballot(b[c] == M);
+    asm("s_bitcmp1_b64 %1, %2\n\ts_cselect_b32 %0, %3, %0" : "+s"(cf) : "s"(mk), "s"(L), "n"(c) : "scc");
+  }
+  return cf;
+}
+
 // Max over all samples of a boxcar array and the first sample reaching it:
 // lane maxima by a max3 tree over groups of three registers, the wave maximum
 // by DPP, the first lane L holding it by a ballot, then the first register of
-// lane L holding it from one ballot per register (compares write lane masks
-// to scalar registers; lane L's bit is tested on the scalar unit).
+// lane L holding it (locate_first).
+constexpr int kShortC = 3;
 template <int C>
 __device__ __forceinline__ void max_first(const float (&b)[C], float& M, int& T) {
   constexpr int G = (C + 2) / 3;
@@ -167,19 +297,14 @@ __device__ __forceinline__ void max_first(const float (&b)[C], float& M, int& T)
   float m = g[0];
 #pragma unroll
   for (int k = 1; k < G; k += 2) m = (k + 1 < G) ? fmaxf(m, fmaxf(g[k], g[k + 1])) : fmaxf(m, g[k]);
-  M = wave_max_f(m);
+  // (a few samples per lane: the widths' reductions are short enough to run
+  // interleaved, which the compiler does with its own form; 1 sample: 188
+  // against 203 us for the 75x-binned survey quarter)
+  M = C <= kShortC ? wave_max_f(m) : wave_max_uniform(m);
   // some lane's maximum equals M, so the ballot is never empty
   const int L = __ffsll((long long)ballot(m == M)) - 1;
-  int cf = C - 1;
-#pragma unroll
-  for (int c = C - 2; c >= 0; --c) {
-    // cf = c if lane L's bit of the compare mask is set: s_bitcmp1_b64 tests
-    // the bit straight into SCC (two scalar instructions per register; the
-    // compiler's mask-and-compare form takes three)
-    const uint64_t mk = ballot(b[c] == M);
-    asm("s_bitcmp1_b64 %1, %2\n\ts_cselect_b32 %0, %3, %0" : "+s"(cf) : "s"(mk), "s"(L), "n"(c) : "scc");
-  }
-  T = (M > kNegInf) ? C * L + cf : -1;
+  const int cf = locate_first<C>(b, M, L);
+  T = __float_as_int(M) != __float_as_int(kNegInf) ? C * L + cf : -1;      // (never NaN)
 }
 
 // Where one cube's results go.
@@ -201,10 +326,18 @@ struct Reporter {
   float snr_lane;
   int toa_lane;
   float norm_lane;          // lane iw: sqrt(n_sub * width[iw])
+  template <int C>
   __device__ __forceinline__ void emit(int iw, float M, int T) {
-    const bool mine = lane_id() == iw;
-    snr_lane = mine ? M : snr_lane;
-    toa_lane = mine ? T : toa_lane;
+    if constexpr (C <= kShortC) {
+      const bool mine = lane_id() == iw;
+      snr_lane = mine ? M : snr_lane;
+      toa_lane = mine ? T : toa_lane;
+    } else {
+      // (volatile, as is wave_max_uniform: one width's maximum is located before
+      // the next one's is formed; put off, it would keep both sums in registers)
+      asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(snr_lane) : "s"(M), "n"(iw));
+      asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(toa_lane) : "s"(T), "n"(iw));
+    }
   }
   __device__ __forceinline__ void flush() {
     const int l = lane_id();
@@ -231,9 +364,9 @@ struct Reporter {
     float M;
     int T;
     max_first<C>(b, M, T);
-    emit(iw, M, T);
+    emit<C>(iw, M, T);
   }
-  __device__ __forceinline__ void invalid(int iw) { emit(iw, kNegInf, -1); }
+  __device__ __forceinline__ void invalid() { snr_lane = kNegInf; toa_lane = -1; }   // a trial with no valid sample
 };
 
 // Everything the search needs about one cube (also the batch descriptor).
@@ -348,16 +481,13 @@ __device__ __forceinline__ void search_group(const CubeDesc& cd, int p0, ST* zl,
       dmax_next = dn < n_dm ? cd.dmax[dn] : 0;
       rep.d = d;
       if (dmax_d >= n_t) {
-        for (int iw = 0; iw < NSFRB_NW; ++iw) rep.invalid(iw);
+        rep.invalid();
         rep.flush();
         continue;
       }
       for (int pass = 0; pass < NSFRB_NPASS; ++pass) {
         float cur[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) cur[c] = 0.f;
-        for (int s = 0; s < n_sub; ++s)
-          add_row<C>(cur, zbase + s * rs, __builtin_amdgcn_readlane(dl_cur, s), l);
+        dedisperse<C>(cur, zbase, rs, n_sub, [&](int s) { return __builtin_amdgcn_readlane(dl_cur, s); }, l);
         nsfrb_chain<C>(pass, cur, rep);
       }
       rep.flush();
@@ -518,6 +648,21 @@ __device__ __forceinline__ void fill_tails(ST* buf, int n_sub, int n_t, int rs) 
   }
 }
 
+// Delays of the trial a wave takes in round rd, sub-band s's in lane s.
+struct RoundDelays {
+  int now, next;
+};
+template <int NW>
+__device__ __forceinline__ int round_delays(const int* delays, int n_dm, int n_sub, int rd, int wv, int l) {
+  const int d = min(rd * NW + wv, n_dm - 1);
+  return l < n_sub ? delays[(size_t)d * n_sub + l] : 0;
+}
+template <int C, int NW>
+__device__ __forceinline__ RoundDelays first_delays(const int* delays, int n_dm, int n_sub, int wv, int l) {
+  if constexpr (!split_rows(C)) return RoundDelays{0, 0};
+  return RoundDelays{round_delays<NW>(delays, n_dm, n_sub, 0, wv, l), round_delays<NW>(delays, n_dm, n_sub, 1, wv, l)};
+}
+
 // The DM trials of one pixel whose rows are in zl; `release` runs once every
 // wave has read the rows for the last time (after the last round's
 // de-dispersion; it is called by every wave, and must contain the barrier
@@ -525,21 +670,32 @@ __device__ __forceinline__ void fill_tails(ST* buf, int n_sub, int n_t, int rs) 
 // registers): waves past the last trial repeat it (writing the same values
 // twice), and a trial with no valid sample is searched with zero delays (its
 // row of `delays` holds zeros) and then reported as -inf / -1.
+// Delays: rows read in halves keep them in lanes (a scalar load between their
+// LDS reads would make every wait a wait for all of them). dl holds the wave's
+// delays of rounds 0 and 1, requested before any row request; those of later
+// rounds are requested two rounds ahead. Other rows read each row's delay
+// through the scalar cache.
 template <int C, int NW, bool PAR = false, class Release>
 __device__ __forceinline__ void search_pixel_dms(const CubeDesc& cd, const int* delays, const int* dmaxv,
-                                                 const ST* zl, Reporter& rep, int wv, int l, Release&& release,
-                                                 int par = 0) {
+                                                 RoundDelays dl, const ST* zl, Reporter& rep, int wv, int l,
+                                                 Release&& release, int par = 0) {
   const int n_dm = cd.n_dm, n_t = cd.n_t, n_sub = cd.n_sub, rs = cd.rs;
   const int n_rounds = (n_dm + NW - 1) / NW;
   for (int rd = 0; rd < n_rounds; ++rd) {
     const int d = min(rd * NW + wv, n_dm - 1);
     const int* dd = delays + (size_t)d * n_sub;
+    const int dlv = dl.now + (PAR ? row_offset(par, l, n_t) : 0);
+    if constexpr (split_rows(C)) {
+      dl.now = dl.next;
+      if (rd + 2 < n_rounds) dl.next = round_delays<NW>(delays, n_dm, n_sub, rd + 2, wv, l);
+    }
     for (int pass = 0; pass < NSFRB_NPASS; ++pass) {
       float cur[C];
-#pragma unroll
-      for (int c = 0; c < C; ++c) cur[c] = 0.f;
-      for (int s = 0; s < n_sub; ++s)    // (PAR: rows placed at their parity offset, see stage_rows_par)
-        add_row<C>(cur, zl + s * rs, ld_const(dd + s) + (PAR ? row_offset(par, s, n_t) : 0), l);
+      // (PAR: rows placed at their parity offset, see stage_rows_par)
+      dedisperse<C>(cur, zl, rs, n_sub, [&](int s) {
+        if constexpr (split_rows(C)) return __builtin_amdgcn_readlane(dlv, s);
+        else return ld_const(dd + s) + (PAR ? row_offset(par, s, n_t) : 0);
+      }, l);
       if (pass == NSFRB_NPASS - 1 && rd == n_rounds - 1) release();
       // a wave in its boxcar chain issues ahead of waves reading rows (the
       // row readers mostly wait on the LDS; raising the chain measured 8%
@@ -618,10 +774,11 @@ __device__ __forceinline__ ItemWalk xcd_walk(long long n) {
 // LDS buffers, at the start of the pixel). No vector-memory load is issued
 // while row requests are in flight (one counter tracks them all): delays and
 // DM bounds come through the scalar cache, the S/N normalisers are read once.
-template <int C, int NW, int NBUF>
+template <int LC, int NW, int NBUF>
 __device__ __forceinline__ void search_persistent(const CubeDesc& cd, const int* __restrict__ delays,
                                                   const int* __restrict__ dmaxv) {
-  extern __shared__ unsigned char lds_raw[];
+  constexpr int C = lane_samples(LC);
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   __shared__ Best red[NW];
   const int wv = __builtin_amdgcn_readfirstlane(tid_x() / kWave);
   const int l = lane_id();
@@ -629,6 +786,7 @@ __device__ __forceinline__ void search_persistent(const CubeDesc& cd, const int*
   ST* bufs = reinterpret_cast<ST*>(lds_raw);
   for (int b = 0; b < NBUF; ++b) fill_tails<NW>(bufs + b * tile, cd.n_sub, cd.n_t, cd.rs);
   const float norm_l = lane_norm(cd, l);
+  const RoundDelays dl = first_delays<C, NW>(delays, cd.n_dm, cd.n_sub, wv, l);   // the same for every pixel
   const ItemWalk r = xcd_walk<NW>(cd.n_pix);
   long long k = r.k0, i = r.item(k);
   if (i < r.n) stage_rows_async<NW>(cd, (int)i, bufs, wv, l);
@@ -641,7 +799,7 @@ __device__ __forceinline__ void search_persistent(const CubeDesc& cd, const int*
     __syncthreads();
     if (NBUF == 2 && i_next < r.n) stage_rows_async<NW>(cd, (int)i_next, bufs + ((it + 1) & 1) * tile, wv, l);
     Reporter rep{CubeOut{cd.norms, cd.snr_max, cd.toa, cd.n_pix}, p, 0, Best{kNegInf, -1, -1, -1}, 0.f, 0, norm_l};
-    search_pixel_dms<C, NW>(cd, delays, dmaxv, zl, rep, wv, l, [&]() {
+    search_pixel_dms<C, NW>(cd, delays, dmaxv, dl, zl, rep, wv, l, [&]() {
       if (NBUF == 1) {
         __syncthreads();   // no wave reads the rows of p again
         if (i_next < r.n) stage_rows_async<NW>(cd, (int)i_next, bufs, wv, l);
@@ -663,12 +821,13 @@ __device__ __forceinline__ void search_persistent(const CubeDesc& cd, const int*
 // delays: the -inf tails are written for each item, and each cube's rows are
 // copied with the copy its alignment allows (dma_w). buf_stride: elements
 // between the LDS buffers (PIX tiles of the class's largest size each).
-template <int C, int NW, int NBUF, int PIX>
+template <int LC, int NW, int NBUF, int PIX>
 __device__ __forceinline__ void search_batch_persistent(const CubeDesc* __restrict__ descs, int n_cubes,
                                                         long long n_items, int buf_stride) {
+  constexpr int C = lane_samples(LC);
   static_assert(NW % PIX == 0, "every pixel of an item gets the same number of waves");
   constexpr int WPP = NW / PIX;
-  extern __shared__ unsigned char lds_raw[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   __shared__ Best red[NW];
   const int wv = __builtin_amdgcn_readfirstlane(tid_x() / kWave);
   const int l = lane_id();
@@ -679,8 +838,10 @@ __device__ __forceinline__ void search_batch_persistent(const CubeDesc* __restri
     while (c + 1 < n_cubes && i >= ld_const(&descs[c + 1].item_begin)) ++c;
     return c;
   };
+  RoundDelays dl_item{0, 0};                       // of the item requested last
   auto stage = [&](int c, long long i, ST* buf) {
     const CubeDesc cd = ld_const(descs + c);
+    dl_item = first_delays<C, WPP>(cd.delays, cd.n_dm, cd.n_sub, wq, l);
     const int p0 = (int)(i - cd.item_begin) * PIX;
 #pragma unroll
     for (int k = 0; k < PIX; ++k) {
@@ -707,11 +868,12 @@ __device__ __forceinline__ void search_batch_persistent(const CubeDesc* __restri
       for (int k2 = 0; k2 < PIX; ++k2)
         fix_row_ends<NW>(cd, min(p0 + k2, cd.n_pix - 1), buf + k2 * tile_stride, wv, l);
     __syncthreads();
+    const RoundDelays dl = dl_item;
     if (NBUF == 2 && i_next < r.n) stage(c_next, i_next, bufs + ((it + 1) & 1) * buf_stride);
     Reporter rep{CubeOut{cd.norms, cd.snr_max, cd.toa, cd.n_pix}, p0 + slot, 0, Best{kNegInf, -1, -1, -1}, 0.f, 0,
                  lane_norm(cd, l)};
     const int par = (sizeof(ST) == 2 && cd.dma_w == 2) ? row_parity(cd, min(p0 + slot, cd.n_pix - 1)) : 0;
-    search_pixel_dms<C, WPP, true>(cd, cd.delays, cd.dmax, buf + slot * tile_stride, rep, wq, l, [&]() {
+    search_pixel_dms<C, WPP, true>(cd, cd.delays, cd.dmax, dl, buf + slot * tile_stride, rep, wq, l, [&]() {
       if (NBUF == 1) {
         __syncthreads();   // no wave reads the rows of this item again
         if (i_next < r.n) stage(c_next, i_next, bufs);
@@ -728,10 +890,11 @@ __device__ __forceinline__ void search_batch_persistent(const CubeDesc* __restri
 
 // Single cube: work item i covers pixels [i*PIX, i*PIX + PIX); items are dealt
 // so that the items running on one XCD at a time are neighbours.
-template <int C, int PIX, int NW>
+template <int LC, int PIX, int NW>
 __device__ __forceinline__ void search_cube(const nsfrb::CubeDesc& cd) {
   using namespace nsfrb;
-  extern __shared__ unsigned char lds_raw[];
+  constexpr int C = lane_samples(LC);
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   __shared__ Best red[NW];
   ST* zl = reinterpret_cast<ST*>(lds_raw);
   const int n_items = (cd.n_pix + PIX - 1) / PIX;

@@ -14,6 +14,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <set>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -152,18 +153,11 @@ extern "C" nsfrb_status nsfrb_plan_delays(const nsfrb_search_config* cfg, int32_
 
 // ------------------------------------------------- search plan (codegen)
 struct KernelClass {
-  int C;     // samples per lane
+  int C;     // length class (see length_class)
   int PIX;   // pixels per workgroup
   int NW;    // waves per workgroup (8 or 16)
 };
 std::string single_kernel_name(const KernelClass& k);
-// Samples per lane: odd, so 64 lanes reading rows at a common delay hit
-// distinct LDS banks; 64*C > n_time, so every series ends in padding.
-// Samples per lane C: 64 C > n_time, so every series has a -inf padding sample.
-// FP32 rows are read one sample per register and C is odd: lanes C samples
-// apart hit distinct LDS banks. FP16 rows are read two samples per dword and C
-// is even with C/2 odd: every lane then starts on the same half of a dword (the
-// parity of the delay) and lanes C/2 dwords apart hit distinct banks.
 // DM-trial grid from a smearing tolerance (see nsfrb.h): with A = 4.15 ms *
 // (nu_min^-2 - nu_max^-2), B = 0.0083 ms * dnu * nu_min^-3, C^2 = W_int^2 + t_s^2
 // and q = tol^2 - 1, the half spacing h after trial D solves
@@ -205,9 +199,14 @@ extern "C" nsfrb_status nsfrb_plan_dm_grid(double nu_min_ghz, double nu_max_ghz,
   return NSFRB_OK;
 }
 
-static int samples_per_lane(int n_time, int store) {
+// Samples per lane C: 64 C > n_time, so every series has a -inf padding sample.
+// One sample per read: C odd, so that lanes C samples apart hit distinct LDS
+// banks. Paired reads: C even with C/2 odd, so that every lane starts on the
+// same half of a pair (the parity of the delay) and lanes C/2 pairs apart hit
+// distinct banks.
+static int samples_per_lane(int n_time, bool paired) {
   int c = (n_time + 64) / 64;
-  if (store == NSFRB_F16) {
+  if (paired) {
     if (c & 1) c += 1;
     if (((c / 2) & 1) == 0) c += 2;
   } else if ((c & 1) == 0) {
@@ -215,13 +214,34 @@ static int samples_per_lane(int n_time, int store) {
   }
   return c;
 }
-// Row length in samples: 64 C + the largest searched delay + 1 (whole dwords for FP16).
+// Length class of a plan (its kernels' names and template arguments): the
+// samples per lane of FP16 rows read in pairs, of other rows read singly.
+static int length_class(int n_time, int store) { return samples_per_lane(n_time, store == NSFRB_F16); }
+// Row length in samples: 64 C + the largest searched delay + 1, even (16-bit
+// rows start on a dword, rows read in pairs on a pair).
 static int row_len(int C, int dmax_search, int store) {
   const int rs = 64 * C + dmax_search + 1;
-  return store == NSFRB_F32 ? rs : (rs + 1) & ~1;      // 16-bit rows start on a dword
+  return store == NSFRB_F32 && (C & 1) ? rs : (rs + 1) & ~1;
 }
 static size_t lds_bytes_for(int pix, int n_sub, int rs, int store) {
   return (size_t)pix * n_sub * rs * dtype_size(store);
+}
+static bool rows_fit(int n_sub, int lanes, int dmax_search, int store) {
+  return lds_bytes_for(1, n_sub, (row_len(lanes, dmax_search, store) + 7) & ~7, store) <= kLdsBudget;
+}
+// Samples per lane of a plan. FP16 rows are always read in pairs; FP32 and BF16
+// rows where that costs little: pairs may need up to three samples more per
+// lane than single reads, every one of them boxcar work, while they save half
+// of the LDS time of the row reads (FP32: up to 8% more samples; BF16, whose
+// single reads are 16 bits wide, up to 25%). The longer rows must fit in LDS
+// (with the 16-byte row pitch of the batch and persistent kernels). A lean plan
+// reads singly.
+static int plan_samples_per_lane(int n_time, int store, int n_sub, int dmax_search, bool lean) {
+  const int lc = length_class(n_time, store);
+  if (store == NSFRB_F16 || lean) return lc;
+  const int c = samples_per_lane(n_time, true);
+  if (100 * c > (store == NSFRB_F32 ? 108 : 125) * lc) return lc;
+  return rows_fit(n_sub, c, dmax_search, store) ? c : lc;
 }
 
 // Emit the boxcar plan: power-of-two levels by pairwise doubling, other
@@ -292,6 +312,95 @@ static nsfrb_status gen_chain(const std::vector<int>& widths, std::string& out, 
   return NSFRB_OK;
 }
 
+// Specialisation of locate_first for C samples per lane: lane L's maximum is
+// first looked for among the group maxima, in order, and then only in the group
+// that holds it. The branches stay inside one asm block: between C++ blocks they
+// made the compiler spill the boxcar arrays. The group maxima are formed again
+// (two or three instructions for each group tested): kept in registers from the
+// maximum tree they saved 4% of the instructions of a survey trial, but width
+// lists that already fill the registers spilled. %0 result, %1 scratch, %2 M,
+// %3 L, then the registers b[0..C).
+static constexpr int kSplitC = 20;         // samples per lane from which rows are read in two parts, as in k_search_body.h
+static constexpr int kArgGroup = 5;
+static constexpr int kArgGroupedC = 17;    // fewer samples per lane keep one compare per register
+static std::string gen_locate(int C) {
+  const int G = (C + kArgGroup - 1) / kArgGroup;
+  std::ostringstream o;
+  o << "namespace nsfrb {\ntemplate <>\n__device__ __forceinline__ int locate_first<" << C << ">(const float (&b)[" << C
+    << "], float M, int L) {\n  int cf;\n  float t;\n  asm(\n";
+  auto line = [&](const std::string& text) { o << "    \"" << text << "\\n\"\n"; };
+  auto reg = [](int c) { return "%" + std::to_string(4 + c); };
+  auto test = [&](const std::string& v) {
+    line("v_cmp_eq_f32_e32 vcc, %2, " + v);
+    line("s_bitcmp1_b64 vcc, %3");
+  };
+  for (int k = 0; k + 1 < G; ++k) {          // (every group but the last has kArgGroup registers)
+    const int c = kArgGroup * k;
+    line("v_max3_f32 %1, " + reg(c) + ", " + reg(c + 1) + ", " + reg(c + 2));
+    line("v_max3_f32 %1, %1, " + reg(c + 3) + ", " + reg(c + 4));
+    test("%1");
+    line("s_cbranch_scc1 .Lg" + std::to_string(k) + "_%=");
+  }
+  for (int k = G - 1; k >= 0; --k) {
+    const int lo = kArgGroup * k, hi = std::min(C, lo + kArgGroup) - 1;
+    if (k < G - 1) line(".Lg" + std::to_string(k) + "_%=:");
+    line("s_movk_i32 %0, " + std::to_string(hi));
+    for (int c = hi - 1; c >= lo; --c) {
+      test(reg(c));
+      line("s_cselect_b32 %0, " + std::to_string(c) + ", %0");
+    }
+    if (k > 0) line("s_branch .Le_%=");
+  }
+  o << "    \".Le_%=:\"\n    : \"=&s\"(cf), \"=&v\"(t) : \"s\"(M), \"s\"(L)";
+  for (int c = 0; c < C; ++c) o << ", \"v\"(b[" << c << "])";
+  o << " : \"vcc\", \"scc\");\n  return cf;\n}\n}\n";
+  return o.str();
+}
+
+// add_pairs for N samples of a lane's row read in pairs: %i (i < N) the sums,
+// then the pairs (FP32: each sample a register, the sample after them last;
+// 16-bit: N/2 + 1 dwords), then the delay, whose parity is the first sample's
+// place in its pair. BF16 samples are moved into place through a scratch
+// register, %N.
+static std::string gen_add_pairs(int N, int store) {
+  std::ostringstream o;
+  const bool f32 = store == DT_F32, bf16 = store == DT_BF16;
+  const int in = N + (bf16 ? 1 : 0), n_in = f32 ? N + 1 : N / 2 + 1;
+  const char* args = f32 ? "const float2* w, float end, int dl" : bf16 ? "const uint32_t* w, bf16_t, int dl"
+                                                                       : "const uint32_t* w, _Float16, int dl";
+  o << "namespace nsfrb {\ntemplate <>\n__device__ __forceinline__ void add_pairs<" << N << ">(float* cur, " << args
+    << ") {\n" << (bf16 ? "  uint32_t t;\n" : "") << "  asm(\"s_bitcmp1_b32 %" << in + n_in
+    << ", 0\\n\\ts_cbranch_scc1 .Lodd_%=\\n\"\n";
+  for (int odd = 0; odd < 2; ++odd) {
+    if (odd) o << "    \"s_branch .Lend_%=\\n.Lodd_%=:\\n\"\n";
+    for (int i = 0; i < N; ++i) {
+      const int at = i + odd, dword = in + at / 2, high = at % 2;
+      o << "    \"";
+      if (f32)
+        o << "v_add_f32_e32 %" << i << ", %" << i << ", %" << in + at;
+      else if (bf16)
+        o << (high ? "v_and_b32_e32 %" : "v_lshlrev_b32_e32 %") << N << (high ? ", 0xffff0000, %" : ", 16, %") << dword
+          << "\\n\\tv_add_f32_e32 %" << i << ", %" << i << ", %" << N;
+      else
+        o << "v_fma_mix_f32 %" << i << ", %" << dword << ", 1.0, %" << i << (high ? " op_sel:[1,0,0]" : "")
+          << " op_sel_hi:[1,0,0]";
+      o << "\\n\"\n";
+    }
+  }
+  o << "    \".Lend_%=:\"\n    : ";
+  for (int i = 0; i < N; ++i) o << (i ? ", " : "") << "\"+v\"(cur[" << i << "])";
+  if (bf16) o << ", \"=&v\"(t)";
+  o << "\n    : ";
+  if (f32) {
+    for (int i = 0; i < N; ++i) o << "\"v\"(w[" << i / 2 << "]." << (i % 2 ? "y" : "x") << "), ";
+    o << "\"v\"(end), ";
+  } else {
+    for (int k = 0; k <= N / 2; ++k) o << "\"v\"(w[" << k << "]), ";
+  }
+  o << "\"s\"(dl) : \"scc\");\n}\n}\n";
+  return o.str();
+}
+
 static const char* store_type_name(int store) {
   return store == DT_F32 ? "float" : (store == DT_F16 ? "_Float16" : "nsfrb::bf16_t");
 }
@@ -306,28 +415,52 @@ struct BatchKernel {
 };
 // Translation unit with the per-DM kernels of `single` (C, PIX, NW), the
 // persistent single-cube kernels, and one persistent batch kernel per entry of
-// `batch`.
+// `batch`; lanes: samples per lane of each length class.
 static std::string gen_source(int store, int nw, int npass, const std::string& chain,
                               const std::vector<KernelClass>& single, const std::vector<BatchKernel>& batch,
-                              const std::vector<PersistentKernel>& persistent = {}) {
+                              const std::vector<PersistentKernel>& persistent, const std::map<int, int>& lanes, bool lean) {
   std::ostringstream o;
   o << "#define NSFRB_RTC_PROLOGUE 1\n#include \"device_common.h\"\n";
+  o << "#define NSFRB_LEAN " << (lean ? 1 : 0) << "\n";
   o << "#define NSFRB_NPASS " << npass << "\n";
   o << "typedef " << store_type_name(store) << " ST;\n";
   o << "#define NSFRB_NW " << nw << "\n";
+  o << "constexpr int lane_samples(int lc) { return ";
+  for (const auto& l : lanes)
+    if (l.first != l.second) o << "lc == " << l.first << " ? " << l.second << " : ";
+  o << "lc; }\n";
   o << "#include \"k_search_body.h\"\n";
+  std::set<int> cs, parts;                 // parts: samples of a part of a row read in pairs (k_search_body.h: dedisperse)
+  for (const auto& l : lanes) cs.insert(l.second);
+  for (int c : cs) {
+    if (c >= kArgGroupedC && !lean) o << gen_locate(c);
+    if (c % 2) continue;
+    const int half = (c / 2 + 1) & ~1;
+    if (c >= kSplitC && !lean) parts.insert({half, c - half});
+    else parts.insert(c);
+  }
+  for (int n : parts) o << gen_add_pairs(n, store);
   o << chain;
+  // Two 8-wave workgroups share a CU where their rows leave room: at most 128
+  // VGPRs. Width lists with accumulators need a few more at 30 to 34 samples per
+  // lane (FP16 survey: 130), which a few bytes of spill make up for; other
+  // series stay below by themselves or would spill too much.
+  const bool acc = chain.find("copy_arr") != std::string::npos;
+  auto bounds = [&](int C, int NW) {
+    const bool cap = NW == 8 && acc && lanes.at(C) >= 30 && lanes.at(C) <= 34 && !lean;
+    return "__launch_bounds__(" + std::to_string(64 * NW) + ")" + (cap ? " __attribute__((amdgpu_waves_per_eu(4)))" : "");
+  };
   for (const auto& k : single)
-    o << "extern \"C\" __global__ __launch_bounds__(" << 64 * k.NW << ") void " << single_kernel_name(k)
+    o << "extern \"C\" __global__ " << bounds(k.C, k.NW) << " void " << single_kernel_name(k)
       << "(nsfrb::CubeDesc cd) { search_cube<" << k.C << ", " << k.PIX << ", " << k.NW << ">(cd); }\n";
   for (const auto& k : persistent)
-    o << "extern \"C\" __global__ __launch_bounds__(" << 64 * k.NW << ") void nsfrb_persistent_c" << k.C << "_w"
+    o << "extern \"C\" __global__ " << bounds(k.C, k.NW) << " void nsfrb_persistent_c" << k.C << "_w"
       << k.NW << "_b" << k.n_buf
       << "(nsfrb::CubeDesc cd, const int* __restrict__ delays, const int* __restrict__ dmax) { "
          "nsfrb::search_persistent<" << k.C << ", " << k.NW << ", " << k.n_buf << ">(cd, delays, dmax); }\n";
   // one persistent kernel per class of the batch
   for (size_t i = 0; i < batch.size(); ++i)
-    o << "extern \"C\" __global__ __launch_bounds__(" << 64 * batch[i].NW << ") void nsfrb_batch_kernel_" << i
+    o << "extern \"C\" __global__ " << bounds(batch[i].C, batch[i].NW) << " void nsfrb_batch_kernel_" << i
       << "(const nsfrb::CubeDesc* __restrict__ descs, int n_cubes, long long n_items, int buf_stride) {\n"
          "  nsfrb::search_batch_persistent<" << batch[i].C << ", " << batch[i].NW << ", " << batch[i].n_buf << ", "
       << batch[i].pix << ">(descs, n_cubes, n_items, buf_stride);\n}\n";
@@ -446,12 +579,12 @@ static int persistent_buffers(size_t tile, int nw) {
   return wgs(2) >= std::min(wgs(1), std::max(1, 16 / nw)) ? 2 : 1;
 }
 
-static bool plan_persistent(int n_sub, int n_t, int C, int dmax_search, int store, int NW, PersistentPlan& out) {
+static bool plan_persistent(int n_sub, int n_t, int lanes, int dmax_search, int store, int NW, PersistentPlan& out) {
   out = PersistentPlan{};
   out.NW = NW;
   if (((size_t)n_t * dtype_size(store)) % 16 != 0) return false;
   const int align = store == DT_F32 ? 4 : 8;
-  out.rs = (64 * C + dmax_search + 1 + align - 1) / align * align;
+  out.rs = (64 * lanes + dmax_search + 1 + align - 1) / align * align;
   const size_t tile = (size_t)n_sub * out.rs * dtype_size(store);
   out.n_buf = persistent_buffers(tile, NW);
   out.lds = out.n_buf * tile;
@@ -459,12 +592,12 @@ static bool plan_persistent(int n_sub, int n_t, int C, int dmax_search, int stor
 }
 
 // 16 waves when there are at least 16 DM trials, and 8.
-static std::vector<PersistentPlan> persistent_candidates(int n_dm, int n_sub, int n_t, int C, int dmax_search,
+static std::vector<PersistentPlan> persistent_candidates(int n_dm, int n_sub, int n_t, int lanes, int dmax_search,
                                                          int store) {
   std::vector<PersistentPlan> out;
   for (int NW : {16, 8}) {
     PersistentPlan pp;
-    if ((NW == 8 || n_dm >= NW) && plan_persistent(n_sub, n_t, C, dmax_search, store, NW, pp)) out.push_back(pp);
+    if ((NW == 8 || n_dm >= NW) && plan_persistent(n_sub, n_t, lanes, dmax_search, store, NW, pp)) out.push_back(pp);
   }
   return out;
 }
@@ -480,8 +613,9 @@ extern "C" int nsfrb_debug_plan_source(const nsfrb_search_config* cfg, char* out
   std::vector<int32_t> dl;
   compute_delays(*cfg, dl);
   const int dmax_search = max_delay_searchable(dl, cfg->n_dm, cfg->n_sub, cfg->n_time, nullptr);
-  const int C = samples_per_lane(cfg->n_time, cfg->store_dtype);
-  const int rs = row_len(C, dmax_search, cfg->store_dtype);
+  const int C = length_class(cfg->n_time, cfg->store_dtype);
+  const int lanes = plan_samples_per_lane(cfg->n_time, cfg->store_dtype, cfg->n_sub, dmax_search, false);
+  const int rs = row_len(lanes, dmax_search, cfg->store_dtype);
   std::vector<KernelClass> ks = plan_candidates(C, cfg->n_dm, cfg->n_sub, rs, cfg->store_dtype);
   if (ks.empty()) {
     fail(NSFRB_ERR_UNSUPPORTED, "a pixel's rows do not fit in LDS");
@@ -496,13 +630,13 @@ extern "C" int nsfrb_debug_plan_source(const nsfrb_search_config* cfg, char* out
     return -1;
   std::vector<PersistentKernel> pks;
   std::vector<BatchKernel> bks;          // batch kernels of the same shapes, one and two pixels per item
-  for (const PersistentPlan& pp : persistent_candidates(cfg->n_dm, cfg->n_sub, cfg->n_time, C, dmax_search,
+  for (const PersistentPlan& pp : persistent_candidates(cfg->n_dm, cfg->n_sub, cfg->n_time, lanes, dmax_search,
                                                         cfg->store_dtype)) {
     pks.push_back({C, pp.NW, pp.n_buf});
     bks.push_back({C, pp.NW, pp.n_buf, 1});
     bks.push_back({C, pp.NW, 1, 2});
   }
-  const std::string src = gen_source(cfg->store_dtype, cfg->n_width, npass, chain, ks, bks, pks);
+  const std::string src = gen_source(cfg->store_dtype, cfg->n_width, npass, chain, ks, bks, pks, {{C, lanes}}, false);
   if (out && cap > 0) std::snprintf(out, (size_t)cap, "%s", src.c_str());
   if (compile) {
     std::vector<char> code;
@@ -517,7 +651,8 @@ struct nsfrb_search {
   std::vector<double> freqs, dms;
   std::vector<int32_t> widths, delays, dmaxv;
   int n_pix = 0, device = 0;
-  int C = 0, rs = 0, pix = 1, nw = 8;  // chosen kernel class and LDS row length
+  int C = 0, pix = 1, nw = 8;          // chosen kernel class
+  int lanes = 0, rs = 0;               // samples per lane and LDS row length
   int dmax_search = 0;                 // largest delay of a searchable trial
   int max_acc = kMaxAccumulators;      // accumulators per pass of the boxcar plan (no register spills)
   std::vector<KernelClass> cands;      // per-DM shapes that fit LDS
@@ -583,6 +718,21 @@ static void release(nsfrb_search* h) {
 
 static nsfrb_status autotune(nsfrb_search* h, const std::vector<KernelClass>& ks);
 
+// Length class, samples per lane, LDS row length and per-DM shapes of the handle's plan.
+static void plan_rows(nsfrb_search* h, bool lean) {
+  const nsfrb_search_config& c = h->cfg;
+  h->C = length_class(c.n_time, c.store_dtype);
+  h->lanes = plan_samples_per_lane(c.n_time, c.store_dtype, c.n_sub, h->dmax_search, lean);
+  h->rs = row_len(h->lanes, h->dmax_search, c.store_dtype);
+  h->cands = plan_candidates(h->C, c.n_dm, c.n_sub, h->rs, c.store_dtype);
+}
+
+// First plan to compile: 0 is the tuned one, later ones are lean with ever
+// fewer accumulators. Above 36 samples per lane a list of more than 16 widths
+// is not tried tuned: such plans spill and take a minute to compile (4096
+// samples with 32 widths: 61 s here, lean 38 s).
+static int first_attempt(int C, int n_width) { return C > 36 && n_width > 16 ? 1 : 0; }
+
 // Compiles the handle's kernels (dropping shapes that would spill), sizes the
 // persistent grids and runs the autotuner.
 static nsfrb_status plan_kernels(nsfrb_search* h) {
@@ -592,26 +742,30 @@ static nsfrb_status plan_kernels(nsfrb_search* h) {
   // Only kernels that keep the boxcar chain in registers (up to a few dozen
   // bytes of spill) are ever launched: each compiled candidate's scratch use is
   // queried and a heavily spilling one is dropped. If every shape spills, the
-  // plan is regenerated with fewer accumulators per pass (more passes, each
-  // re-forming the de-dispersed series) before the configuration is refused.
+  // plan is regenerated lean (fewest registers), then with fewer accumulators
+  // per pass (more passes, each re-forming the de-dispersed series), before the
+  // configuration is refused.
   const int allowance = scratch_allowance();
   std::vector<KernelClass> usable;
   // NSFRB_PERSISTENT: "0" per-DM kernel only; "NW" only the persistent kernel of NW waves (studies)
   const char* pers_env = std::getenv("NSFRB_PERSISTENT");
   const int pers_only = pers_env ? std::atoi(pers_env) : -1;
-  for (int max_acc = kMaxAccumulators; max_acc >= 1 && usable.empty(); --max_acc) {
+  for (int attempt = first_attempt(h->C, cfg->n_width); attempt <= kMaxAccumulators && usable.empty(); ++attempt) {
+    const bool lean = attempt > 0;
+    const int max_acc = kMaxAccumulators - std::max(0, attempt - 1);
+    plan_rows(h, lean);
     std::string chain;
     int npass = 1;
     st = gen_chain(h->widths, chain, &npass, max_acc);
     if (st != NSFRB_OK) return st;
     std::vector<PersistentPlan> pps;
     if (pers_only != 0)
-      for (const PersistentPlan& pp : persistent_candidates(cfg->n_dm, cfg->n_sub, cfg->n_time, h->C, h->dmax_search,
+      for (const PersistentPlan& pp : persistent_candidates(cfg->n_dm, cfg->n_sub, cfg->n_time, h->lanes, h->dmax_search,
                                                             cfg->store_dtype))
         if (pers_only < 0 || pp.NW == pers_only) pps.push_back(pp);
     std::vector<PersistentKernel> pks;
     for (const PersistentPlan& pp : pps) pks.push_back({h->C, pp.NW, pp.n_buf});
-    h->source = gen_source(cfg->store_dtype, cfg->n_width, npass, chain, h->cands, {}, pks);
+    h->source = gen_source(cfg->store_dtype, cfg->n_width, npass, chain, h->cands, {}, pks, {{h->C, h->lanes}}, lean);
     st = load_module(h->device, h->source, &h->mod);
     if (st != NSFRB_OK) return st;
     for (const KernelClass& k : h->cands) {
@@ -674,9 +828,7 @@ static nsfrb_status search_create(const nsfrb_search_config* cfg, bool plan_now,
   h->device = cfg->device;
   compute_delays(h->cfg, h->delays);
   h->dmax_search = max_delay_searchable(h->delays, cfg->n_dm, cfg->n_sub, cfg->n_time, &h->dmaxv);
-  h->C = samples_per_lane(cfg->n_time, cfg->store_dtype);
-  h->rs = row_len(h->C, h->dmax_search, cfg->store_dtype);
-  h->cands = plan_candidates(h->C, cfg->n_dm, cfg->n_sub, h->rs, cfg->store_dtype);
+  plan_rows(h.get(), false);
   if (h->cands.empty())
     return fail(NSFRB_ERR_UNSUPPORTED, "n_sub x (padded n_time + max delay) does not fit in LDS for this store dtype");
   const char* force = std::getenv("NSFRB_FORCE_ALLOC_FAIL");
@@ -1100,11 +1252,11 @@ extern "C" nsfrb_status nsfrb_search_plan_info(const nsfrb_search* h, int32_t* i
 }
 
 // ------------------------------------------------------------------- batch
-// One kernel class of a batch: the cubes whose tuned plan has this (C, PIX).
-// One kernel class of a batch: the cubes with the same samples per lane (C) and
-// waves per workgroup; one persistent kernel walks all their pixels.
+// One kernel class of a batch: the cubes of the same length class (C); one
+// persistent kernel walks all their pixels.
 struct BatchClass {
   KernelClass k;                         // C, PIX (pixels per work item), NW
+  int lanes = 0;                         // samples per lane
   int n_buf = 1;                         // LDS buffers (PIX tiles each)
   int buf_stride = 0;                    // elements between the buffers (PIX times the class's largest tile)
   hipFunction_t fn = nullptr;
@@ -1158,40 +1310,21 @@ static int batch_pixels_per_item(int C, int nw, int env, size_t tile) {
   return pix;
 }
 
-extern "C" nsfrb_status nsfrb_batch_create(const nsfrb_search_config* cfgs, int32_t n_cubes, nsfrb_batch** out) {
-  g_last_error.clear();
-  if (!out || !cfgs || n_cubes < 1) return fail(NSFRB_ERR_INVALID_ARG, "need cfgs, n_cubes >= 1 and out");
-  *out = nullptr;
-  const nsfrb_search_config& c0 = cfgs[0];
-  for (int i = 0; i < n_cubes; ++i) {
-    const nsfrb_search_config& c = cfgs[i];
-    nsfrb_status st = validate(&c);
-    if (st != NSFRB_OK) return fail(st, "cube " + std::to_string(i) + ": " + g_last_error);
-    bool same = c.n_dm == c0.n_dm && c.n_width == c0.n_width && c.store_dtype == c0.store_dtype &&
-                c.in_dtype == c0.in_dtype && c.norm == c0.norm && c.layout == c0.layout && c.device == c0.device;
-    for (int d = 0; same && d < c.n_dm; ++d) same = c.dm[d] == c0.dm[d];
-    for (int w = 0; same && w < c.n_width; ++w) same = c.width[w] == c0.width[w];
-    if (!same) return fail(NSFRB_ERR_INVALID_ARG, "cube " + std::to_string(i) + " differs in DMs, widths, dtypes, "
-                                                  "normalisation, layout or device");
-  }
-  std::unique_ptr<nsfrb_batch, void (*)(nsfrb_batch*)> b(new nsfrb_batch, batch_release);
-  b->device = c0.device;
-  b->store = c0.store_dtype;
-  b->nw = c0.n_width;
-  for (int i = 0; i < n_cubes; ++i) {
-    nsfrb_search* h = nullptr;
-    nsfrb_status st = search_create(&cfgs[i], false, &h);
-    if (st != NSFRB_OK) return fail(st, "cube " + std::to_string(i) + ": " + g_last_error);
-    b->cubes.push_back(h);
-  }
-  // kernel classes: cubes with the same samples per lane; 16 waves when there
+// Kernel classes, work items and descriptors of a batch's cubes.
+static nsfrb_status batch_classes(nsfrb_batch* b, bool lean) {
+  // kernel classes: cubes of the same length class; 16 waves when there
   // are at least 16 DM trials (the trials are shared by all cubes), else 8
+  const nsfrb_search_config& c0 = b->cubes[0]->cfg;
   const int nw_b = c0.n_dm >= 16 ? 16 : 8;
   int pix_env = 0;
   if (const char* e = std::getenv("NSFRB_BATCH_PIX")) pix_env = std::atoi(e);
   const size_t sz = dtype_size(c0.store_dtype);
   const int align = c0.store_dtype == DT_F32 ? 4 : 8;          // row pitch: whole 16-byte vectors
   std::vector<int> cls_of(b->cubes.size());
+  b->classes.clear();
+  b->descs.clear();
+  b->n_items = 0;
+  for (nsfrb_search* h : b->cubes) plan_rows(h, lean);
   for (size_t i = 0; i < b->cubes.size(); ++i) {
     nsfrb_search* h = b->cubes[i];
     int cls = -1;
@@ -1207,6 +1340,21 @@ extern "C" nsfrb_status nsfrb_batch_create(const nsfrb_search_config* cfgs, int3
   b->desc_of_cube.assign(b->cubes.size(), -1);
   for (size_t c = 0; c < b->classes.size(); ++c) {
     BatchClass& bc = b->classes[c];
+    // the class's cubes share its kernel's samples per lane: paired reads only
+    // where the rows of every one of them are read so
+    for (size_t i = 0; i < b->cubes.size(); ++i)
+      if (cls_of[i] == (int)c) bc.lanes = std::max(bc.lanes, b->cubes[i]->lanes);
+    for (size_t i = 0; i < b->cubes.size(); ++i)
+      if (cls_of[i] == (int)c &&
+          (b->cubes[i]->lanes == bc.k.C || !rows_fit(b->cubes[i]->cfg.n_sub, bc.lanes, b->cubes[i]->dmax_search, c0.store_dtype))) {
+        bc.lanes = bc.k.C;
+        break;
+      }
+    for (size_t i = 0; i < b->cubes.size(); ++i)
+      if (cls_of[i] == (int)c) {
+        b->cubes[i]->lanes = bc.lanes;
+        b->cubes[i]->rs = row_len(bc.lanes, b->cubes[i]->dmax_search, c0.store_dtype);
+      }
     int tile1 = 0;                       // the class's largest one-pixel tile (elements)
     for (size_t i = 0; i < b->cubes.size(); ++i)
       if (cls_of[i] == (int)c)
@@ -1233,21 +1381,59 @@ extern "C" nsfrb_status nsfrb_batch_create(const nsfrb_search_config* cfgs, int3
     bc.lds = bc.n_buf * tile;
     b->n_items += bc.n_items;
   }
+  return NSFRB_OK;
+}
+
+extern "C" nsfrb_status nsfrb_batch_create(const nsfrb_search_config* cfgs, int32_t n_cubes, nsfrb_batch** out) {
+  g_last_error.clear();
+  if (!out || !cfgs || n_cubes < 1) return fail(NSFRB_ERR_INVALID_ARG, "need cfgs, n_cubes >= 1 and out");
+  *out = nullptr;
+  const nsfrb_search_config& c0 = cfgs[0];
+  for (int i = 0; i < n_cubes; ++i) {
+    const nsfrb_search_config& c = cfgs[i];
+    nsfrb_status st = validate(&c);
+    if (st != NSFRB_OK) return fail(st, "cube " + std::to_string(i) + ": " + g_last_error);
+    bool same = c.n_dm == c0.n_dm && c.n_width == c0.n_width && c.store_dtype == c0.store_dtype &&
+                c.in_dtype == c0.in_dtype && c.norm == c0.norm && c.layout == c0.layout && c.device == c0.device;
+    for (int d = 0; same && d < c.n_dm; ++d) same = c.dm[d] == c0.dm[d];
+    for (int w = 0; same && w < c.n_width; ++w) same = c.width[w] == c0.width[w];
+    if (!same) return fail(NSFRB_ERR_INVALID_ARG, "cube " + std::to_string(i) + " differs in DMs, widths, dtypes, "
+                                                  "normalisation, layout or device");
+  }
+  std::unique_ptr<nsfrb_batch, void (*)(nsfrb_batch*)> b(new nsfrb_batch, batch_release);
+  b->device = c0.device;
+  b->store = c0.store_dtype;
+  b->nw = c0.n_width;
+  for (int i = 0; i < n_cubes; ++i) {
+    nsfrb_search* h = nullptr;
+    nsfrb_status st = search_create(&cfgs[i], false, &h);
+    if (st != NSFRB_OK) return fail(st, "cube " + std::to_string(i) + ": " + g_last_error);
+    b->cubes.push_back(h);
+  }
   // one module with a persistent kernel per class; like a single cube's plan it
-  // is regenerated with fewer accumulators per pass while a class kernel would
-  // spill more than a search kernel may, and refused only after that
+  // is regenerated lean, then with fewer accumulators per pass, while a class
+  // kernel would spill more than a search kernel may, and refused only after that
   HIP_TRY(hipSetDevice(b->device));
   int n_cu = 0;
   HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, b->device));
-  std::vector<BatchKernel> ks;
-  for (const auto& bc : b->classes) ks.push_back({bc.k.C, bc.k.NW, bc.n_buf, bc.k.PIX});
   bool fits = false;
-  for (int max_acc = kMaxAccumulators; max_acc >= 1 && !fits; --max_acc) {
+  int c_max = 0;
+  for (const nsfrb_search* h : b->cubes) c_max = std::max(c_max, h->C);
+  for (int attempt = first_attempt(c_max, b->nw); attempt <= kMaxAccumulators && !fits; ++attempt) {
+    const bool lean = attempt > 0;
+    nsfrb_status st = batch_classes(b.get(), lean);
+    if (st != NSFRB_OK) return st;
+    std::vector<BatchKernel> ks;
+    std::map<int, int> lanes;
+    for (const auto& bc : b->classes) {
+      ks.push_back({bc.k.C, bc.k.NW, bc.n_buf, bc.k.PIX});
+      lanes[bc.k.C] = bc.lanes;
+    }
     std::string chain;
     int npass = 1;
-    nsfrb_status st = gen_chain(b->cubes[0]->widths, chain, &npass, max_acc);
+    st = gen_chain(b->cubes[0]->widths, chain, &npass, kMaxAccumulators - std::max(0, attempt - 1));
     if (st != NSFRB_OK) return st;
-    st = load_module(b->device, gen_source(b->store, b->nw, npass, chain, {}, ks), &b->mod);
+    st = load_module(b->device, gen_source(b->store, b->nw, npass, chain, {}, ks, {}, lanes, lean), &b->mod);
     if (st != NSFRB_OK) return st;
     fits = true;
     for (size_t c = 0; c < b->classes.size(); ++c) {
