@@ -827,7 +827,6 @@ hipError_t launch_zero_u64(unsigned long long* p, hipStream_t st) {
 }
 
 hipError_t launch_stats(const StatsLaunch& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, a.flag_count);
   switch (a.in_dtype) {
     case DT_F32: return launch_stats_in<float>(a, st);
     case DT_F16: return launch_stats_in<_Float16>(a, st);

@@ -682,12 +682,11 @@ struct nsfrb_search {
   int32_t *d_best_d = nullptr, *d_best_w = nullptr, *d_best_t = nullptr;
   unsigned long long* d_keys = nullptr;
   int32_t* d_count = nullptr;
-  nsfrb_candidate* d_cands = nullptr;
-  int32_t* d_nout = nullptr;
-  unsigned long long* d_flags = nullptr;
-  // pinned host mirrors
+  unsigned long long* d_flags = nullptr;   // zero between runs
+  bool flags_dirty = false;                // a run was cut short between its statistics and its candidate list
+  // pinned host memory the candidate kernels write
   nsfrb_candidate* h_cands = nullptr;
-  int32_t* h_nout = nullptr;
+  int32_t* h_nout = nullptr;               // records, total, flagged (64 bits)
   hipEvent_t done = nullptr;
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   bool profiling = false, ran = false, ext_set = false;
@@ -704,7 +703,7 @@ static void release(nsfrb_search* h) {
   hipSetDevice(h->device);
   void* bufs[] = {h->d_delays, h->d_dmax, h->d_norms, h->d_z, h->d_med, h->d_sig, h->d_ext_med, h->d_ext_sig,
                   h->d_snr, h->d_toa, h->d_best_s, h->d_best_d, h->d_best_w, h->d_best_t, h->d_keys,
-                  h->d_count, h->d_cands, h->d_nout, h->d_flags};
+                  h->d_count, h->d_flags};
   for (void* b : bufs)
     if (b) hipFree(b);
   if (h->d_delays_zeroed) hipFree(h->d_delays_zeroed);
@@ -853,10 +852,8 @@ static nsfrb_status search_create(const nsfrb_search_config* cfg, bool plan_now,
   HIP_TRY(dalloc(&h->d_best_d, n_pix));
   HIP_TRY(dalloc(&h->d_best_w, n_pix));
   HIP_TRY(dalloc(&h->d_best_t, n_pix));
-  HIP_TRY(dalloc(&h->d_keys, n_pix));
-  HIP_TRY(dalloc(&h->d_count, 4));
-  HIP_TRY(dalloc(&h->d_cands, (size_t)cfg->max_candidates));
-  HIP_TRY(dalloc(&h->d_nout, 4));
+  HIP_TRY(dalloc(&h->d_keys, std::max(n_pix, (size_t)cand_counters())));
+  HIP_TRY(dalloc(&h->d_count, (size_t)cand_counters()));
   HIP_TRY(dalloc(&h->d_flags, 1));
   HIP_TRY(hipHostMalloc((void**)&h->h_cands, sizeof(nsfrb_candidate) * cfg->max_candidates, hipHostMallocDefault));
   HIP_TRY(hipHostMalloc((void**)&h->h_nout, sizeof(int32_t) * 4, hipHostMallocDefault));
@@ -868,6 +865,7 @@ static nsfrb_status search_create(const nsfrb_search_config* cfg, bool plan_now,
   HIP_TRY(hipMemcpy(h->d_dmax, h->dmaxv.data(), h->dmaxv.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(h->d_norms, norms.data(), norms.size() * sizeof(float), hipMemcpyHostToDevice));
   HIP_TRY(hipMemset(h->d_flags, 0, sizeof(unsigned long long)));
+  HIP_TRY(hipMemset(h->d_count, 0, sizeof(int32_t) * cand_counters()));
   {
     std::vector<int32_t> dz(h->delays);
     for (int d = 0; d < cfg->n_dm; ++d)
@@ -1063,6 +1061,22 @@ static nsfrb_status autotune(nsfrb_search* h, const std::vector<KernelClass>& ks
 
 static nsfrb_status run_impl(nsfrb_search* h, const void* d_cube, int t_start, void* stream);
 
+static CandDesc cand_desc(const nsfrb_search* h) {
+  const nsfrb_search_config& c = h->cfg;
+  CandDesc d{h->d_best_s, h->d_best_d, h->d_best_w, h->d_best_t, h->d_keys, h->d_count, h->h_cands, h->h_nout,
+             h->d_flags, h->n_pix, c.nx, c.max_candidates, c.snr_threshold, 0, 0};
+  plan_candidates_list(d);
+  return d;
+}
+
+// Before a run's first launch: the counters its kernels add to are zero unless
+// the last run failed half-way.
+static nsfrb_status begin_run(nsfrb_search* h, hipStream_t st) {
+  if (h->flags_dirty) HIP_TRY(launch_zero_u64(h->d_flags, st));
+  h->flags_dirty = true;
+  return NSFRB_OK;
+}
+
 extern "C" nsfrb_status nsfrb_search_run(nsfrb_search* h, const void* d_cube, void* stream) {
   g_last_error.clear();
   return run_impl(h, d_cube, 0, stream);
@@ -1078,30 +1092,32 @@ static nsfrb_status run_impl(nsfrb_search* h, const void* d_cube, int t_start, v
   HIP_TRY(hipSetDevice(h->device));
   const nsfrb_search_config& c = h->cfg;
   if (h->profiling) HIP_TRY(hipEventRecord(h->ev[0], st));
+  nsfrb_status s0 = begin_run(h, st);
+  if (s0 != NSFRB_OK) return s0;
   const void* z = d_cube;
   if (c.layout == NSFRB_LAYOUT_TSP) {
     StatsLaunch sa{d_cube, c.n_time, c.n_sub, h->n_pix, c.norm, c.in_dtype, c.store_dtype,
                    h->d_ext_med, h->d_ext_sig, h->d_med, h->d_sig, h->d_z, h->d_flags, t_start};
     HIP_TRY(launch_stats(sa, st));
     z = h->d_z;
-  } else {
-    HIP_TRY(launch_zero_u64(h->d_flags, st));
   }
   h->last_z = z;
   if (h->profiling) HIP_TRY(hipEventRecord(h->ev[1], st));
   nsfrb_status s2 = launch_search(h, z, st);
   if (s2 != NSFRB_OK) return s2;
   if (h->profiling) HIP_TRY(hipEventRecord(h->ev[2], st));
-  CandLaunch ca{h->d_best_s, h->d_best_d, h->d_best_w, h->d_best_t, h->n_pix, c.nx, c.max_candidates,
-                c.snr_threshold, h->d_keys, h->d_count, h->d_cands, h->d_nout};
-  HIP_TRY(launch_candidates(ca, st));
+  HIP_TRY(launch_candidates(cand_desc(h), st));
+  h->flags_dirty = false;
   if (h->profiling) HIP_TRY(hipEventRecord(h->ev[3], st));
-  HIP_TRY(hipMemcpyAsync(h->h_nout, h->d_nout, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(h->h_cands, h->d_cands, sizeof(nsfrb_candidate) * c.max_candidates,
-                         hipMemcpyDeviceToHost, st));
   HIP_TRY(hipEventRecord(h->done, st));
   h->ran = true;
   return NSFRB_OK;
+}
+
+static int64_t flagged_last_run(const nsfrb_search* h) {
+  int64_t v;
+  std::memcpy(&v, h->h_nout + 2, sizeof v);
+  return v;
 }
 
 static nsfrb_status wait_run(const nsfrb_search* h) {
@@ -1212,9 +1228,7 @@ extern "C" nsfrb_status nsfrb_flag_count_get(nsfrb_search* h, int64_t* count) {
   g_last_error.clear();
   nsfrb_status st = wait_run(h);
   if (st != NSFRB_OK) return st;
-  unsigned long long v = 0;
-  HIP_TRY(hipMemcpy(&v, h->d_flags, sizeof(v), hipMemcpyDeviceToHost));
-  if (count) *count = (int64_t)v;
+  if (count) *count = flagged_last_run(h);
   return NSFRB_OK;
 }
 
@@ -1273,6 +1287,8 @@ struct nsfrb_batch {
   std::vector<CubeDescHost> descs;        // grouped by class; item_begin relative to the class
   std::vector<int> desc_of_cube;          // cube index -> descriptor index
   CubeDescHost* d_descs = nullptr;
+  CandDesc* d_cands = nullptr;            // every cube's candidate list, where all are short
+  int cand_blocks = 0;                    // workgroups of the largest of them (0: one launch per cube)
   long long n_items = 0;
   hipModule_t mod = nullptr;
   hipStream_t cap_stream = nullptr;
@@ -1291,6 +1307,7 @@ static void batch_release(nsfrb_batch* b) {
   if (b->graph) hipGraphDestroy(b->graph);
   if (b->cap_stream) hipStreamDestroy(b->cap_stream);
   if (b->d_descs) hipFree(b->d_descs);
+  if (b->d_cands) hipFree(b->d_cands);
   if (b->done) hipEventDestroy(b->done);
   for (auto* h : b->cubes) release(h);
   delete b;
@@ -1456,6 +1473,16 @@ extern "C" nsfrb_status nsfrb_batch_create(const nsfrb_search_config* cfgs, int3
     bc.grid = (unsigned)std::max(1LL, std::min(g, bc.n_items));
   }
   HIP_TRY(dalloc(&b->d_descs, b->descs.size()));
+  std::vector<CandDesc> cands;
+  bool short_lists = true;
+  for (const nsfrb_search* h : b->cubes) {
+    cands.push_back(cand_desc(h));
+    short_lists = short_lists && cands.back().per > 0;
+    b->cand_blocks = std::max(b->cand_blocks, cands.back().blocks);
+  }
+  if (!short_lists) b->cand_blocks = 0;
+  HIP_TRY(dalloc(&b->d_cands, cands.size()));
+  HIP_TRY(hipMemcpy(b->d_cands, cands.data(), cands.size() * sizeof(CandDesc), hipMemcpyHostToDevice));
   HIP_TRY(hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
   HIP_TRY(hipEventCreateWithFlags(&b->done, hipEventDisableTiming));
   *out = b.release();
@@ -1490,7 +1517,6 @@ static nsfrb_status batch_stats(nsfrb_batch* b, const void* const* d_cubes, hipS
       HIP_TRY(launch_stats(sa, st));
       h->last_z = h->d_z;
     } else {
-      HIP_TRY(launch_zero_u64(h->d_flags, st));
       h->last_z = d_cubes[i];
     }
   }
@@ -1498,16 +1524,28 @@ static nsfrb_status batch_stats(nsfrb_batch* b, const void* const* d_cubes, hipS
 }
 
 static nsfrb_status batch_candidates(nsfrb_batch* b, hipStream_t st) {
+  if (b->cand_blocks) {
+    HIP_TRY(launch_candidates_batch(b->d_cands, (int)b->cubes.size(), b->cand_blocks, st));
+    return NSFRB_OK;
+  }
+  for (auto* h : b->cubes) HIP_TRY(launch_candidates(cand_desc(h), st));
+  return NSFRB_OK;
+}
+
+// The flag counters before a run (outside any captured graph) and after it.
+static nsfrb_status batch_begin(nsfrb_batch* b, hipStream_t st) {
   for (auto* h : b->cubes) {
-    const nsfrb_search_config& c = h->cfg;
-    CandLaunch ca{h->d_best_s, h->d_best_d, h->d_best_w, h->d_best_t, h->n_pix, c.nx, c.max_candidates,
-                  c.snr_threshold, h->d_keys, h->d_count, h->d_cands, h->d_nout};
-    HIP_TRY(launch_candidates(ca, st));
-    HIP_TRY(hipMemcpyAsync(h->h_nout, h->d_nout, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(h->h_cands, h->d_cands, sizeof(nsfrb_candidate) * c.max_candidates,
-                           hipMemcpyDeviceToHost, st));
+    nsfrb_status s = begin_run(h, st);
+    if (s != NSFRB_OK) return s;
   }
   return NSFRB_OK;
+}
+static void batch_done(nsfrb_batch* b) {
+  for (auto* h : b->cubes) {
+    h->ran = true;
+    h->flags_dirty = false;
+  }
+  b->ran = true;
 }
 
 static nsfrb_status batch_enqueue(nsfrb_batch* b, const void* const* d_cubes, hipStream_t st) {
@@ -1551,6 +1589,8 @@ extern "C" nsfrb_status nsfrb_batch_run(nsfrb_batch* b, const void* const* d_cub
     HIP_TRY(hipMemcpy(b->d_descs, b->descs.data(), b->descs.size() * sizeof(CubeDescHost), hipMemcpyHostToDevice));
     b->desc_ptrs = ptrs;
   }
+  nsfrb_status s0 = batch_begin(b, st);
+  if (s0 != NSFRB_OK) return s0;
   if (!b->use_graph) {
     nsfrb_status s = batch_enqueue(b, d_cubes, st);
     if (s != NSFRB_OK) return s;
@@ -1575,8 +1615,7 @@ extern "C" nsfrb_status nsfrb_batch_run(nsfrb_batch* b, const void* const* d_cub
     b->last_graph = true;
   }
   HIP_TRY(hipEventRecord(b->done, st));
-  for (auto* h : b->cubes) h->ran = true;
-  b->ran = true;
+  batch_done(b);
   return NSFRB_OK;
 }
 
@@ -1592,7 +1631,9 @@ extern "C" nsfrb_status nsfrb_batch_run_separate(nsfrb_batch* b, const void* con
       nsfrb_status s = plan_kernels(h);
       if (s != NSFRB_OK) return s;
     }
-  nsfrb_status s = batch_stats(b, d_cubes, st);
+  nsfrb_status s = batch_begin(b, st);
+  if (s != NSFRB_OK) return s;
+  s = batch_stats(b, d_cubes, st);
   if (s != NSFRB_OK) return s;
   for (auto* h : b->cubes) {
     s = launch_search_per_dm(h, h->last_z, st);
@@ -1601,8 +1642,7 @@ extern "C" nsfrb_status nsfrb_batch_run_separate(nsfrb_batch* b, const void* con
   s = batch_candidates(b, st);
   if (s != NSFRB_OK) return s;
   HIP_TRY(hipEventRecord(b->done, st));
-  for (auto* h : b->cubes) h->ran = true;
-  b->ran = true;
+  batch_done(b);
   b->last_graph = false;
   return NSFRB_OK;
 }
@@ -1856,9 +1896,7 @@ extern "C" nsfrb_status nsfrb_stream_push(nsfrb_stream* s, const void* d_chunk, 
   r.searched = 1;
   r.search_ms = ms;
   if (ms > s->deadline_ms) s->drop_next = true;
-  unsigned long long flags = 0;
-  HIP_TRY(hipMemcpy(&flags, s->search->d_flags, sizeof(flags), hipMemcpyDeviceToHost));
-  r.flagged = (int64_t)flags;
+  r.flagged = flagged_last_run(s->search);
   if (s->search->h_nout[0] > 0) {            // one candidate per batch: the window's best
     r.has_candidate = 1;
     r.cand = s->search->h_cands[0];

@@ -22,19 +22,27 @@ struct StatsLaunch {
 hipError_t launch_stats(const StatsLaunch& a, hipStream_t st);
 hipError_t launch_zero_u64(unsigned long long* p, hipStream_t st);
 
-struct CandLaunch {
+// One cube's candidate list. keys, count and flags are device memory, out and
+// n_out pinned host memory the device writes.
+struct CandDesc {
   const float* best_snr;
   const int* best_d;
   const int* best_w;
   const int* best_t;
+  unsigned long long* keys;   // [max(n_pix, blocks * k_max)] scratch
+  int* count;                 // [cand_counters()] zero before a run and after it
+  void* out;                  // [k_max] nsfrb_candidate records
+  int* n_out;                 // [4]: records written, total, flagged (64 bits)
+  unsigned long long* flags;  // flag counter of the run, left at zero
   int n_pix, nx, k_max;
   float theta;
-  unsigned long long* keys;   // [n_pix] scratch
-  int* count;                 // [1] number of pixels >= theta
-  void* out;                  // [k_max] nsfrb_candidate records
-  int* n_out;                 // [2]: records written, total
+  int per, blocks;            // plan_candidates_list: pixels per thread and workgroups (0: long list)
 };
-hipError_t launch_candidates(const CandLaunch& a, hipStream_t st);
+void plan_candidates_list(CandDesc& d);
+int cand_counters();
+hipError_t launch_candidates(const CandDesc& a, hipStream_t st);
+// Every cube of a batch; all have per > 0.
+hipError_t launch_candidates_batch(const CandDesc* descs, int n, int max_blocks, hipStream_t st);
 
 }  // namespace nsfrb
 

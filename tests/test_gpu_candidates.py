@@ -1,0 +1,92 @@
+"""Candidate lists at the edges of their kernels (needs an MI355X).
+
+One sample, one sub-band, one DM and width 1: a pixel's best S/N is its own
+sample, so every list is known exactly. Sizes lie at one pixel per thread
+block, at the changes of pixels per thread and at the longest list that is
+merged; values are distinct, tied at the K-th place, all equal, or all below
+the threshold.
+"""
+import numpy as np
+import pytest
+
+from paper_2510_18136_amd import nsfrb
+from tests._lib import ensure_built
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    ensure_built()
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+
+
+def config(nx, ny, k, theta):
+    return nsfrb.SearchConfig(nx, ny, 1, [1.4], [0.0], [1], norm="none", snr_threshold=theta, max_candidates=k)
+
+
+def values(kind, n, rng):
+    if kind == "distinct":
+        return rng.permutation(n).astype(np.float32) - n // 3          # both signs
+    if kind == "ties":
+        return rng.integers(0, 3, n).astype(np.float32)
+    if kind == "equal":
+        return np.full(n, 7.0, np.float32)
+    return np.full(n, -1e6, np.float32)                                # below
+
+
+def expected(v, theta, k, nx):
+    hit = np.flatnonzero(v >= theta)
+    order = hit[np.lexsort((hit, -v[hit]))][:k]
+    return [(int(p) % nx, int(p) // nx, float(v[p])) for p in order], hit.size
+
+
+def got(s):
+    recs, total, _ = s.candidates()
+    assert all(r["dm_index"] == 0 and r["width_index"] == 0 and r["toa"] == 0 for r in recs)
+    return [(r["x"], r["y"], r["snr"]) for r in recs], total
+
+
+@pytest.mark.parametrize("nx,ny,k", [(1, 1, 1), (255, 1, 10), (16, 16, 10), (1025, 1, 10), (64, 64, 16),
+                                     (201, 150, 100), (256, 256, 256), (256, 256, 257), (700, 600, 10),
+                                     (128, 128, 4096)])
+@pytest.mark.parametrize("kind", ["distinct", "ties", "equal", "below"])
+def test_lists(nx, ny, k, kind):
+    v = values(kind, nx * ny, np.random.default_rng(nx + k))
+    theta = -50.0 if kind == "distinct" else 1.0
+    x = torch.from_numpy(v).cuda()
+    with nsfrb.Search(config(nx, ny, k, theta)) as s:
+        print(f"[gpu] candidates {nx}x{ny} K={k} {kind}", flush=True)
+        for _ in range(2):                             # the counters are left ready for the next run
+            s.run(x.data_ptr())
+            assert got(s) == expected(v, theta, k, nx)
+
+
+def test_flag_count_of_each_run():
+    v = np.zeros(4096, np.float32)
+    bad = v.copy()
+    bad[[3, 77, 4095]] = np.nan
+    with nsfrb.Search(config(64, 64, 10, 1.0)) as s:
+        for cube, n in ((bad, 3), (v, 0), (bad, 3), (bad, 3)):
+            x = torch.from_numpy(cube).cuda()
+            s.run(x.data_ptr())
+            assert s.flag_count() == n
+
+
+def test_batch_lists():
+    """Cubes of every size in one launch, graph replays with other values in between."""
+    rng = np.random.default_rng(9)
+    shapes = [(1, 1), (33, 31), (64, 64), (200, 150), (300, 300)]
+    cfgs = [config(nx, ny, 12, 1.0) for nx, ny in shapes]
+    xs = [torch.zeros(nx * ny, device="cuda") for nx, ny in shapes]
+    with nsfrb.Batch(cfgs) as b:
+        for kind in ("ties", "below", "equal", "ties"):
+            vs = [values(kind, nx * ny, rng) for nx, ny in shapes]
+            for x, v in zip(xs, vs):
+                x.copy_(torch.from_numpy(v))
+            torch.cuda.synchronize()
+            b.run([x.data_ptr() for x in xs])
+            for i, (nx, ny) in enumerate(shapes):
+                recs, total = b.candidates(i)
+                assert ([(r["x"], r["y"], r["snr"]) for r in recs], total) == expected(vs[i], 1.0, 12, nx)
