@@ -60,7 +60,9 @@ struct nsfrb_classifier {
   uint16_t* d_wf[4] = {};      // BF16 forward weights in convolution-operand order
   uint16_t* d_wb[4] = {};      // BF16 backward-data weights (flipped taps, transposed channels; layers 2..4)
   uint16_t* d_act[4] = {};     // conv outputs a_1..a_4 [n][t][y][x][32]
-  uint16_t* d_dpre[4] = {};    // pre-activation gradients of conv layers 1..4 (kept for inspection)
+  uint16_t* d_dpre[4] = {};    // pre-activation gradients of conv layers 1..4 (kept for inspection; flagged rows only)
+  uint8_t* d_nz[4] = {};       // their row flags [n][t * y]: unflagged rows are zero and not stored
+  uint32_t* d_bad = nullptr;   // samples with a non-finite pre-activation
   float* d_part = nullptr;
   float* d_part_db = nullptr;
   float* d_h = nullptr;         // head input [n][64]: channel maxima, candidate-position features
@@ -87,7 +89,7 @@ void release(nsfrb_classifier* c) {
   if (!c) return;
   hipSetDevice(c->device);
   void* bufs[] = {c->d_theta, c->d_m, c->d_v, c->d_grad, c->d_part, c->d_part_db, c->d_h, c->d_dh, (void*)c->d_arg,
-                  (void*)c->d_pool_part, c->d_hs,
+                  (void*)c->d_pool_part, c->d_hs, (void*)c->d_bad,
                   c->d_logits, c->d_prob, c->d_loss, c->d_cut_desc, c->d_delays, (void*)c->d_cube_ptrs};
   for (void* b : bufs)
     if (b) hipFree(b);
@@ -97,6 +99,8 @@ void release(nsfrb_classifier* c) {
     if (c->d_act[l]) hipFree(c->d_act[l]);
   }
   for (auto* p : c->d_dpre)
+    if (p) hipFree(p);
+  for (auto* p : c->d_nz)
     if (p) hipFree(p);
   if (c->h_loss) hipHostFree(c->h_loss);
   delete c;
@@ -125,7 +129,8 @@ nsfrb_status forward(nsfrb_classifier* c, const uint16_t* x, int n, hipStream_t 
   }
   const uint16_t* in = x;
   for (int l = 0; l < 4; ++l) {
-    NSFRB_HIP_TRY(launch_conv_fwd(kLayerCin[l], in, c->d_wf[l], c->d_theta + kL.b[l], c->d_act[l], n, T, Y, st));
+    NSFRB_HIP_TRY(launch_conv_fwd(kLayerCin[l], in, c->d_wf[l], c->d_theta + kL.b[l], c->d_act[l], n, T, Y, c->d_bad,
+                                  st));
     in = c->d_act[l];
   }
   NSFRB_HIP_TRY(launch_pool(c->d_act[3], n, T * Y * kX, centre_pos(c), c->d_pool_part, c->d_h, c->d_arg, st));
@@ -162,6 +167,12 @@ extern "C" nsfrb_status nsfrb_classifier_create(const nsfrb_classifier_config* c
     NSFRB_HIP_TRY(dalloc(&c->d_act[l], N * npos * kCh));
   }
   for (auto& p : c->d_dpre) NSFRB_HIP_TRY(dalloc(&p, N * npos * kCh));
+  for (auto& p : c->d_nz) {
+    NSFRB_HIP_TRY(dalloc(&p, N * npos / kX));
+    NSFRB_HIP_TRY(hipMemset(p, 0, N * npos / kX));
+  }
+  NSFRB_HIP_TRY(dalloc(&c->d_bad, N));
+  NSFRB_HIP_TRY(hipMemset(c->d_bad, 0, N * sizeof(uint32_t)));
   const size_t items = (size_t)wgrad_items((int)N, cfg->ny);
   NSFRB_HIP_TRY(dalloc(&c->d_part, items * kTap * kCh * kCh));
   NSFRB_HIP_TRY(dalloc(&c->d_part_db, items * kCh));
@@ -338,12 +349,15 @@ extern "C" nsfrb_status nsfrb_classifier_train_step(nsfrb_classifier* c, const v
   if (s != NSFRB_OK) return s;
   NSFRB_HIP_TRY(launch_head(c->d_h, d_labels, n, c->d_theta + kL.head, c->d_hs, c->d_grad + kL.head, c->d_dh, c->d_logits,
                             c->d_prob, c->d_loss, 1, st));
-  NSFRB_HIP_TRY(launch_pool_backward(c->d_dh, c->d_arg, c->d_act[3], n, npos, centre_pos(c), c->d_dpre[3], st));
+  NSFRB_HIP_TRY(launch_row_flags(c->d_arg, n, T, Y, centre_pos(c), c->d_bad, c->d_nz, st));
+  NSFRB_HIP_TRY(launch_pool_backward(c->d_dh, c->d_arg, c->d_act[3], n, npos, centre_pos(c), c->d_nz[3], c->d_dpre[3], st));
   for (int l = 3; l >= 0; --l) {
     const uint16_t* in = l ? c->d_act[l - 1] : x;
     NSFRB_HIP_TRY(launch_conv_wgrad(kLayerCin[l], in, c->d_dpre[l], c->d_part, c->d_part_db, c->d_grad + kL.w[l],
-                                    c->d_grad + kL.b[l], n, T, Y, st));
-    if (l) NSFRB_HIP_TRY(launch_conv_bwd_data(c->d_dpre[l], c->d_wb[l], c->d_act[l - 1], c->d_dpre[l - 1], n, T, Y, st));
+                                    c->d_grad + kL.b[l], n, T, Y, c->d_nz[l], st));
+    if (l)
+      NSFRB_HIP_TRY(launch_conv_bwd_data(c->d_dpre[l], c->d_wb[l], c->d_act[l - 1], c->d_dpre[l - 1], n, T, Y, c->d_nz[l],
+                                         c->d_nz[l - 1], st));
   }
   if (update) {
     c->step += 1;
@@ -384,6 +398,7 @@ extern "C" nsfrb_status nsfrb_classifier_grad_pre_get(nsfrb_classifier* c, int32
   NSFRB_HIP_TRY(hipSetDevice(c->device));
   NSFRB_HIP_TRY(hipDeviceSynchronize());
   const size_t per = (size_t)c->cfg.n_time * c->cfg.ny * kX * kCh;
+  NSFRB_HIP_TRY(launch_zero_rows(c->d_dpre[layer - 1], c->d_nz[layer - 1], n, c->cfg.n_time, c->cfg.ny, nullptr));
   NSFRB_HIP_TRY(hipMemcpy(host_out, c->d_dpre[layer - 1], per * n * sizeof(uint16_t), hipMemcpyDeviceToHost));
   return NSFRB_OK;
 }

@@ -52,6 +52,16 @@ __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint
 // before the matrix work of plane t and stored into the free slot after it. In
 // a staged row the 16-byte channel chunk c of position xs sits at chunk
 // c ^ swz(xs), so the 32 lanes of a B read hit distinct banks.
+//
+// MODE 1 works on sparse rows: the gradient enters at the rows of the pooled
+// maxima and the candidate's own (at most 33 of a sample's T x Y rows) and
+// spreads by one row in t and y per layer, so most rows of dpre are exactly
+// zero. nz_in / nz_out flag the rows of `in` and `out` that may not be
+// (k_row_flags); unflagged rows are neither read, written nor multiplied, which
+// leaves every sum as it was (adding zeros, in the same order). 64 cutouts of
+// 64 x 32 x 32: 299 us per layer with every row, see launch_conv_bwd_data.
+// MODE 0 reports non-finite pre-activations per sample (bad): the backward pass
+// of such a sample keeps every row, since 0 * inf is not 0.
 constexpr int kConvWaves = 8;
 constexpr int kConvYT = kConvWaves;       // output rows (y) per plane per workgroup
 constexpr int kConvRY = kConvYT + 2;      // staged rows per plane (y halo)
@@ -69,7 +79,10 @@ __global__ __launch_bounds__(kConvWaves * kWave) void k_conv3(const uint16_t* __
                                                               const uint16_t* __restrict__ wm,
                                                               const float* __restrict__ bias,
                                                               const uint16_t* __restrict__ mask,
-                                                              uint16_t* __restrict__ out, int N, int T, int Y) {
+                                                              uint16_t* __restrict__ out, int N, int T, int Y,
+                                                              uint32_t* __restrict__ bad,
+                                                              const uint8_t* __restrict__ nz_in,
+                                                              const uint8_t* __restrict__ nz_out) {
   constexpr int G8 = CIN / 8;
   constexpr int S = kTaps * CIN / 16;                    // K steps
   constexpr int ROW = kConvXS * G8;                      // 16-byte chunks per staged row
@@ -92,20 +105,43 @@ __global__ __launch_bounds__(kConvWaves * kWave) void k_conv3(const uint16_t* __
     const int c = i % G8, side = (i / G8) % 2, r = i / (2 * G8);
     xl[r * ROW + (side ? kConvXS - 1 : 0) * G8 + c] = make_uint4(0u, 0u, 0u, 0u);
   }
+  // MODE 1: bit ry of in_rows[tp - t0 + 1] (tp = t0 - 1 .. t1) flags input row
+  // y0 - 1 + ry, bit w of out_rows[t - t0] output row y0 + w
+  __shared__ uint32_t in_rows[kConvTT + 3], out_rows[kConvTT];
+  if constexpr (MODE == 1) {
+    if (tid < kConvTT + 3) in_rows[tid] = 0;
+    if (tid < kConvTT) out_rows[tid] = 0;
+    __syncthreads();
+    for (int i = tid; i < (kConvTT + 2) * kConvRY; i += NT) {
+      const int tp = t0 - 1 + i / kConvRY, ry = i % kConvRY, yr = y0 - 1 + ry;
+      if (tp < 0 || tp >= T || yr < 0 || yr >= Y) continue;
+      const size_t row = ((size_t)n * T + tp) * Y + yr;
+      if (nz_in[row]) atomicOr(&in_rows[tp - t0 + 1], 1u << ry);
+      if (tp >= t0 && tp < t1 && ry >= 1 && ry <= kConvYT && nz_out[row]) atomicOr(&out_rows[tp - t0], 1u << (ry - 1));
+    }
+    __syncthreads();
+  }
+  auto rows_of = [&](int tp) -> uint32_t {       // input rows of plane tp that may be nonzero
+    if constexpr (MODE == 0) return ~0u;
+    else return tp - t0 + 1 < kConvTT + 2 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)in_rows[tp - t0 + 1]) : 0u;
+  };
   // plane tp -> registers (zero outside the cube)
   auto fetch = [&](int tp, uint4 (&v)[PER]) {
+    const uint32_t rows = rows_of(tp);
+    if (MODE == 1 && !rows) return;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const int i = tid + q * NT;
       const int c = i % G8, x = (i / G8) % kXW, ry = i / (G8 * kXW);
       const int y = y0 - 1 + ry;
-      const bool ok = i < PLANE && tp >= 0 && tp < T && y >= 0 && y < Y;
+      const bool ok = i < PLANE && tp >= 0 && tp < T && y >= 0 && y < Y && (MODE == 0 || (rows >> ry & 1));
       v[q] = ok ? reinterpret_cast<const uint4*>(in + ((((size_t)n * T + tp) * Y + y) * kXW + x) * CIN)[c]
                 : make_uint4(0u, 0u, 0u, 0u);
     }
   };
   auto stage = [&](int tp, const uint4 (&v)[PER]) {
-    uint4* sl = xl + (tp & 3) * SLOT;
+    uint4* sl = xl + ((tp + 4) & 3) * SLOT;
+    if (MODE == 1 && !rows_of(tp)) return;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const int i = tid + q * NT;
@@ -119,7 +155,7 @@ __global__ __launch_bounds__(kConvWaves * kWave) void k_conv3(const uint16_t* __
   {
     uint4 v[PER];
     fetch(t0 - 1, v);
-    stage(t0 - 1 + 4, v);            // slot index uses tp & 3; keep it non-negative
+    stage(t0 - 1, v);
     fetch(t0, v);
     stage(t0, v);
     fetch(t0 + 1, v);
@@ -134,20 +170,32 @@ __global__ __launch_bounds__(kConvWaves * kWave) void k_conv3(const uint16_t* __
   const int y = y0 + w;
   const bool row_ok = y < Y;
   const v8bf* wa = reinterpret_cast<const v8bf*>(wl) + l;
+  float nf = 0.0f;                   // 0 unless some pre-activation is infinite or NaN
   for (int t = t0; t < t1; ++t) {
     uint4 v[PER];
+    uint32_t orows = ~0u;
+    if constexpr (MODE == 1) {
+      orows = (uint32_t)__builtin_amdgcn_readfirstlane((int)out_rows[t - t0]);
+      // nothing to compute and nothing to stage: no wave reads or writes the ring in this step
+      if (!orows && !rows_of(t + 2)) continue;
+    }
     fetch(t + 2, v);
-    if (row_ok) {
+    if (row_ok && (MODE == 0 || (orows >> w & 1))) {
       v16f acc = {};
 #pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const int tap = s / (CIN / 16), kb = s % (CIN / 16);
-        const int dt = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-        const uint4* rowp = xl + ((t - 1 + dt + 4) & 3) * SLOT + (w + dy) * ROW + (x + dx) * G8;
-        const uint4 bv = rowp[(2 * kb) ^ hs[dx]];
-        v8bf b;
-        __builtin_memcpy(&b, &bv, 16);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[s * kWave], b, acc, 0, 0, 0);
+      for (int g = 0; g < 9; ++g) {
+        const int dt = g / 3, dy = g % 3;
+        if (MODE == 1 && !(rows_of(t - 1 + dt) >> (w + dy) & 1)) continue;
+#pragma unroll
+        for (int h = 0; h < S / 9; ++h) {
+          const int s = g * (S / 9) + h;                       // K step: tap, then half of the input channels
+          const int dx = h / (CIN / 16), kb = h % (CIN / 16);
+          const uint4* rowp = xl + ((t - 1 + dt + 4) & 3) * SLOT + (w + dy) * ROW + (x + dx) * G8;
+          const uint4 bv = rowp[(2 * kb) ^ hs[dx]];
+          v8bf b;
+          __builtin_memcpy(&b, &bv, 16);
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[s * kWave], b, acc, 0, 0, 0);
+        }
       }
       const size_t pos = (((size_t)n * T + t) * Y + y) * kXW + x;
 #pragma unroll
@@ -162,7 +210,11 @@ __global__ __launch_bounds__(kConvWaves * kWave) void k_conv3(const uint16_t* __
           for (int j = 0; j < 4; ++j) o[j] = f2bf(bf2f(mv[j]) > 0.0f ? acc[4 * g + j] : 0.0f);
         } else {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) o[j] = f2bf(fmaxf(acc[4 * g + j] + bias[c0 + j], 0.0f));
+          for (int j = 0; j < 4; ++j) {
+            const float u = acc[4 * g + j] + bias[c0 + j];
+            nf = __builtin_fmaf(u, 0.0f, nf);
+            o[j] = f2bf(fmaxf(u, 0.0f));
+          }
         }
         uint2 pk;
         pk.x = (uint32_t)o[0] | ((uint32_t)o[1] << 16);
@@ -173,6 +225,7 @@ __global__ __launch_bounds__(kConvWaves * kWave) void k_conv3(const uint16_t* __
     stage(t + 2, v);                 // slot of plane t - 2, which step t does not read
     __syncthreads();
   }
+  if (MODE == 0 && nf != 0.0f) bad[n] = 1u;
 }
 
 // --------------------------------------------------------- weight gradient
@@ -192,8 +245,14 @@ __global__ __launch_bounds__(kConvWaves * kWave) void k_conv3(const uint16_t* __
 // The next plane's loads are issued before the matrix work and stored after
 // it. Each item writes its partial sums, which a second kernel adds in a fixed
 // order (deterministic).
+//
+// Rows of dpre that k_row_flags leaves unflagged are exactly zero: planes
+// without a flagged row are skipped (and input planes that only they would
+// read), and unflagged rows of a plane are not multiplied. The sums are those of
+// all rows, in the same order.
 constexpr int kWgR = 4;                    // output rows per item
 constexpr int kWgWaves = 9;                // one per (dt, dy)
+constexpr int kWgMaxT = 256;               // planes of a cutout
 constexpr int kWgRows = kWgR + 2;          // staged input rows per plane
 constexpr int kWgXP = kXW + 8;             // inT row pitch (bf16): 80 bytes
 constexpr int kWgKP = kWgR * kXW + 8;      // dT row pitch (bf16): 272 bytes
@@ -205,7 +264,7 @@ __global__ __launch_bounds__(kWgWaves * kWave) void k_conv3_wgrad(const uint16_t
                                                                   const uint16_t* __restrict__ dpre,
                                                                   float* __restrict__ part,
                                                                   float* __restrict__ part_db, int N, int T,
-                                                                  int Y) {
+                                                                  int Y, const uint8_t* __restrict__ nz) {
   constexpr int NT = kWgWaves * kWave;
   constexpr int G8 = CIN / 8;
   constexpr int SLOT = kWgRows * CIN * kWgXP;                 // bf16 per ring slot
@@ -224,9 +283,21 @@ __global__ __launch_bounds__(kWgWaves * kWave) void k_conv3_wgrad(const uint16_t
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int dt = w / 3, dy = w % 3;
 
+  // bit r of rows[t + 1]: row y0 + r of plane t is flagged (planes -1 and T: none)
+  __shared__ uint32_t rows[kWgMaxT + 4];
+  for (int i = tid; i < T + 4; i += NT) {
+    uint32_t m = 0;
+    if (i >= 1 && i <= T)
+      for (int r = 0; r < kWgR; ++r)
+        if (y0 + r < Y && nz[((size_t)n * T + i - 1) * Y + y0 + r]) m |= 1u << r;
+    rows[i] = m;
+  }
   // dT entries that no store reaches (the row ends of the shifted copies) stay 0
   for (int i = tid; i < 2 * 3 * DCOPY; i += NT) dT[i] = 0;
   __syncthreads();
+  auto d_rows = [&](int t) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)rows[t + 1]); };   // t = -1 .. T + 2
+  // input plane tp (-1 .. T + 1; zeros outside the cube) is read by the output planes next to it
+  auto in_used = [&](int tp) { return ((tp > 0 ? d_rows(tp - 1) : 0u) | d_rows(tp) | d_rows(tp + 1)) != 0; };
 
   auto fetch_in = [&](int tp, uint4 (&v)[IN_PER]) {
 #pragma unroll
@@ -256,13 +327,14 @@ __global__ __launch_bounds__(kWgWaves * kWave) void k_conv3_wgrad(const uint16_t
   // dpre plane tp (rows y0 .. y0+3) -> one chunk per thread (8 output channels of one position)
   const int dc = tid % (kCH / 8), dxp = (tid / (kCH / 8)) % kXW, dr = tid / (kCH / 8 * kXW);
   auto fetch_d = [&](int tp) {
-    const bool ok = tid < D_CH && tp < T && y0 + dr < Y;
+    const bool ok = tid < D_CH && tp < T && (d_rows(tp) >> dr & 1);
     return ok ? reinterpret_cast<const uint4*>(dpre + ((((size_t)n * T + tp) * Y + y0 + dr) * kXW + dxp) * kCH)[dc]
               : make_uint4(0u, 0u, 0u, 0u);
   };
   float dbp[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto stage_d = [&](int buf, const uint4& v) {
-    if (tid < D_CH) {
+  auto stage_d = [&](int tp, const uint4& v) {
+    const int buf = tp & 1;
+    if (tid < D_CH && (d_rows(tp) >> dr & 1)) {
       const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -280,12 +352,11 @@ __global__ __launch_bounds__(kWgWaves * kWave) void k_conv3_wgrad(const uint16_t
 
   {
     uint4 v[IN_PER];
-    fetch_in(-1, v);
-    stage_in(-1, v);
-    fetch_in(0, v);
-    stage_in(0, v);
-    fetch_in(1, v);
-    stage_in(1, v);
+    for (int tp = -1; tp <= 1; ++tp)
+      if (in_used(tp)) {
+        fetch_in(tp, v);
+        stage_in(tp, v);
+      }
     stage_d(0, fetch_d(0));
   }
   __syncthreads();
@@ -293,13 +364,17 @@ __global__ __launch_bounds__(kWgWaves * kWave) void k_conv3_wgrad(const uint16_t
   v16f acc[3] = {v16f{}, v16f{}, v16f{}};
   const int col = l & 31, h = l >> 5;
   for (int t = 0; t < T; ++t) {
+    const uint32_t now = d_rows(t), next = d_rows(t + 1);
+    const bool more = in_used(t + 2);
+    if (!now && !next && !more) continue;      // nothing read, nothing staged
     uint4 vin[IN_PER];
-    fetch_in(t + 2, vin);
+    if (more) fetch_in(t + 2, vin);
     const uint4 vd = fetch_d(t + 1);
     const uint16_t* sb = inT + ((t - 1 + dt + 4) & 3) * SLOT + col * kWgXP;      // inT[.][ci = col][x]
     const uint16_t* sa = dT + (size_t)(t & 1) * 3 * DCOPY + col * kWgKP;         // dT_dx[co = col][k]
 #pragma unroll
     for (int r = 0; r < kWgR; ++r) {
+      if (!(now >> r & 1)) continue;
 #pragma unroll
       for (int xh = 0; xh < 2; ++xh) {
         const int xo = 16 * xh + 8 * h;
@@ -313,8 +388,8 @@ __global__ __launch_bounds__(kWgWaves * kWave) void k_conv3_wgrad(const uint16_t
         }
       }
     }
-    stage_in(t + 2, vin);            // ring slot of plane t - 2, not read at step t
-    stage_d((t + 1) & 1, vd);        // the other dT buffer
+    if (more) stage_in(t + 2, vin);  // ring slot of plane t - 2, not read at step t
+    stage_d(t + 1, vd);              // the other dT buffer
     __syncthreads();
   }
 
@@ -347,22 +422,76 @@ __global__ __launch_bounds__(kWgWaves * kWave) void k_conv3_wgrad(const uint16_t
 // out[i] = sum over items of part[item][i] in a fixed order (deterministic):
 // a workgroup takes 32 outputs; thread (o, c) adds items c, c + 8, ... of output
 // o, and the eight partial sums are then added in order of c.
+// The last workgroup does the kCH bias gradients.
 constexpr int kRedOut = 32, kRedPar = 8;
-__global__ __launch_bounds__(kRedOut * kRedPar) void k_reduce_items(const float* __restrict__ part, int n_items,
-                                                                    int len, float* __restrict__ out) {
+__global__ __launch_bounds__(kRedOut * kRedPar) void k_reduce_items(const float* __restrict__ part_w,
+                                                                    const float* __restrict__ part_b, int n_items,
+                                                                    int len_w, float* __restrict__ out_w,
+                                                                    float* __restrict__ out_b) {
   __shared__ float ps[kRedPar][kRedOut];
+  const bool bias = blockIdx.x == gridDim.x - 1;
+  const float* part = bias ? part_b : part_w;
+  const int len = bias ? kCH : len_w;
   const int o = threadIdx.x % kRedOut, c = threadIdx.x / kRedOut;
-  const int i = blockIdx.x * kRedOut + o;
+  const int i = (bias ? 0 : blockIdx.x * kRedOut) + o;
   float s = 0.f;
-  if (i < len)
-    for (int it = c; it < n_items; it += kRedPar) s += part[(size_t)it * len + i];
+  if (i < len) {
+    int it = c;
+    for (; it + 7 * kRedPar < n_items; it += 8 * kRedPar) {      // eight loads in flight, added in order
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = part[(size_t)(it + k * kRedPar) * len + i];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s += v[k];
+    }
+    for (; it < n_items; it += kRedPar) s += part[(size_t)it * len + i];
+  }
   ps[c][o] = s;
   __syncthreads();
   if (c == 0 && i < len) {
     float t = ps[0][o];
     for (int k = 1; k < kRedPar; ++k) t += ps[k][o];
-    out[i] = t;
+    (bias ? out_b : out_w)[i] = t;
   }
+}
+
+// Flags of the rows (t, y) of each layer's pre-activation gradient that may
+// hold a nonzero: layer 4's are the rows of the pooled maxima and the
+// candidate's own, layer l's those within 4 - l rows of one of them in t and y
+// (a 3 x 3 x 3 convolution spreads by one). A sample with a non-finite
+// pre-activation (bad, cleared here for the next pass) has every row flagged.
+// One workgroup per sample clears the flags and sets those around each of the
+// 33 rows; nz[l - 1] holds layer l's flags [n][T * Y].
+struct RowFlags {
+  uint8_t* nz[4];
+};
+constexpr int kFlagThreads = 1024;
+__global__ __launch_bounds__(kFlagThreads) void k_row_flags(const int* __restrict__ arg, int T, int Y, int centre,
+                                                            uint32_t* __restrict__ bad, RowFlags f) {
+  const int n = blockIdx.x, rows = T * Y;
+  const uint8_t every = bad[n] != 0;
+#pragma unroll
+  for (int l = 0; l < 4; ++l)
+    for (int r = threadIdx.x; r < rows; r += kFlagThreads) f.nz[l][(size_t)n * rows + r] = every;
+  __syncthreads();
+  if (threadIdx.x == 0) bad[n] = 0;
+  // (a few flags are set more than once, to the same value)
+  for (int i = threadIdx.x; i < (kCH + 1) * 49; i += kFlagThreads) {
+    const int j = i / 49, dt = i % 49 / 7 - 3, dy = i % 7 - 3, far = max(abs(dt), abs(dy));
+    const int row = (j < kCH ? arg[n * kCH + j] : centre) / kXW;
+    const int t = row / Y + dt, y = row % Y + dy;
+    if (t < 0 || t >= T || y < 0 || y >= Y) continue;
+#pragma unroll
+    for (int l = 0; l < 4; ++l)
+      if (far <= 3 - l) f.nz[l][(size_t)n * rows + t * Y + y] = 1;
+  }
+}
+
+// Zeros in the unflagged rows (2 KB each) of a gradient, for whoever reads it whole.
+__global__ void k_zero_rows(uint16_t* __restrict__ dpre, const uint8_t* __restrict__ nz, long long total16) {
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total16;
+       i += (long long)gridDim.x * blockDim.x)
+    if (!nz[i / (kXW * kCH / 8)]) reinterpret_cast<uint4*>(dpre)[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // ------------------------------------------------------------------- head
@@ -421,20 +550,34 @@ __global__ __launch_bounds__(kPoolThreads) void k_pool_partial(const uint16_t* _
   }
 }
 
-__global__ void k_pool_finish(const uint32_t* __restrict__ part, int n_chunks, int chunk, const uint16_t* __restrict__ act,
-                              int N, int npos, int centre, float* __restrict__ h, int* __restrict__ arg) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N * kCH) return;
-  const int n = i / kCH, c = i % kCH;
-  uint32_t best = part[(size_t)n * n_chunks * kCH + c];
-  int g_best = 0;
-  for (int g = 1; g < n_chunks; ++g) {
+// One workgroup per sample: thread (g0, c) takes chunks g0, g0 + 8, ... of channel c.
+constexpr int kFinPar = 8;
+__global__ __launch_bounds__(kFinPar * kCH) void k_pool_finish(const uint32_t* __restrict__ part, int n_chunks, int chunk,
+                                                               const uint16_t* __restrict__ act, int npos, int centre,
+                                                               float* __restrict__ h, int* __restrict__ arg) {
+  __shared__ uint32_t key[kFinPar][kCH];
+  __shared__ int at[kFinPar][kCH];
+  const int n = blockIdx.x, c = threadIdx.x % kCH, g0 = threadIdx.x / kCH;
+  uint32_t best = 0;
+  int g_best = n_chunks;
+  for (int g = g0; g < n_chunks; g += kFinPar) {
     const uint32_t k = part[((size_t)n * n_chunks + g) * kCH + c];
-    if ((k >> 16) > (best >> 16)) { best = k; g_best = g; }            // strictly larger: earlier chunk kept on ties
+    if (g_best == n_chunks || (k >> 16) > (best >> 16)) { best = k; g_best = g; }   // the earlier chunk on ties
   }
-  h[(size_t)n * 2 * kCH + c] = bf2f((uint16_t)(best >> 16));
-  h[(size_t)n * 2 * kCH + kCH + c] = bf2f(act[((size_t)n * npos + centre) * kCH + c]);
-  arg[i] = g_best * chunk + (0xFFFF - (int)(best & 0xFFFFu));
+  key[g0][c] = best;
+  at[g0][c] = g_best;
+  __syncthreads();
+  if (g0 == 0) {
+    for (int q = 1; q < kFinPar; ++q) {
+      const uint32_t k = key[q][c];
+      const int g = at[q][c];
+      if (g < n_chunks && ((k >> 16) > (best >> 16) || ((k >> 16) == (best >> 16) && g < g_best))) { best = k; g_best = g; }
+    }
+    h[(size_t)n * 2 * kCH + c] = bf2f((uint16_t)(best >> 16));
+    arg[n * kCH + c] = g_best * chunk + (0xFFFF - (int)(best & 0xFFFFu));
+  } else if (g0 == 1) {
+    h[(size_t)n * 2 * kCH + kCH + c] = bf2f(act[((size_t)n * npos + centre) * kCH + c]);
+  }
 }
 
 // MLP head (64 -> 32 ReLU -> 1) and BCE-with-logits loss for a batch of n.
@@ -494,16 +637,26 @@ __global__ void k_head_grad(const float* __restrict__ h, const float* __restrict
   float s = 0.f;
   if (p < kCH * kH) {                                                  // W1[j][c]: du_j * h_c
     const int j = p / kH, c = p % kH;
+    
+#pragma unroll 16
     for (int i = 0; i < n; ++i) s += hs[(size_t)i * kHS + j] * h[(size_t)i * kH + c];
   } else if (p < kCH * kH + kCH) {                                     // c1[j]: du_j
     const int j = p - kCH * kH;
+    
+#pragma unroll 16
     for (int i = 0; i < n; ++i) s += hs[(size_t)i * kHS + j];
   } else if (p < kCH * kH + 2 * kCH) {                                 // w2[j]: dz * relu(u_j)
     const int j = p - kCH * kH - kCH;
+    
+#pragma unroll 16
     for (int i = 0; i < n; ++i) s += hs[(size_t)i * kHS + 2 * kCH] * hs[(size_t)i * kHS + kCH + j];
   } else if (p == kHeadParams - 1) {                                   // c2: dz
+    
+#pragma unroll 16
     for (int i = 0; i < n; ++i) s += hs[(size_t)i * kHS + 2 * kCH];
   } else {                                                             // mean loss
+    
+#pragma unroll 16
     for (int i = 0; i < n; ++i) s += hs[(size_t)i * kHS + 2 * kCH + 1];
     loss_out[0] = s / (float)n;
     return;
@@ -513,20 +666,21 @@ __global__ void k_head_grad(const float* __restrict__ h, const float* __restrict
 
 // dpre4[n][pos][c] = bf16(g * (act4[n][pos][c] > 0)) with g = dm[n][c] at the
 // channel's maximum, + dq[n][c] at the candidate position, 0 elsewhere; eight
-// channels (16 bytes) per thread.
-__global__ void k_pool_backward(const float* __restrict__ dh, const int* __restrict__ arg,
-                                const uint16_t* __restrict__ act, int npos, int centre, long long total8,
-                                uint16_t* __restrict__ dpre) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total8;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int cg = (int)(i & 3);
-    const long long r = i >> 2;
-    const int pos = (int)(r % npos);
-    const long long n = r / npos;
+// channels (16 bytes) per thread. Only flagged rows are written, rows j, j + 33,
+// ... by workgroup (j, n).
+constexpr int kRowThreads = kXW * kCH / 8;
+__global__ __launch_bounds__(kRowThreads) void k_pool_backward(const float* __restrict__ dh, const int* __restrict__ arg,
+                                                               const uint16_t* __restrict__ act, int npos, int centre,
+                                                               const uint8_t* __restrict__ nz, uint16_t* __restrict__ dpre) {
+  const int j = blockIdx.x, n = blockIdx.y, rows = npos / kXW;
+  const int cg = threadIdx.x & 3, x = threadIdx.x >> 2;
+  const int* ar = arg + n * kCH + cg * 8;
+  const float* dm = dh + (size_t)n * kH + cg * 8;
+  auto write_row = [&](int row) {
+    const int pos = row * kXW + x;
+    const size_t i = ((size_t)n * npos + pos) * (kCH / 8) + cg;
     const uint4 av = reinterpret_cast<const uint4*>(act)[i];
     const uint32_t aw[4] = {av.x, av.y, av.z, av.w};
-    const int* ar = arg + n * kCH + cg * 8;
-    const float* dm = dh + n * kH + cg * 8;
     uint32_t ow[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -543,7 +697,9 @@ __global__ void k_pool_backward(const float* __restrict__ dh, const int* __restr
       ow[q] = o;
     }
     reinterpret_cast<uint4*>(dpre)[i] = make_uint4(ow[0], ow[1], ow[2], ow[3]);
-  }
+  };
+  for (int row = j; row < rows; row += kCH + 1)
+    if (nz[(size_t)n * rows + row]) write_row(row);
 }
 
 // ------------------------------------------------------------ optimiser
@@ -621,30 +777,30 @@ static unsigned conv_blocks(int N, int T, int Y) {
 }
 
 hipError_t launch_conv_fwd(int cin, const uint16_t* in, const uint16_t* w, const float* bias, uint16_t* out, int N,
-                           int T, int Y, hipStream_t st) {
+                           int T, int Y, uint32_t* bad, hipStream_t st) {
   const dim3 grid(conv_blocks(N, T, Y)), block(kConvWaves * kWave);
-  if (cin == 16) hipLaunchKernelGGL((k_conv3<16, 0>), grid, block, 0, st, in, w, bias, nullptr, out, N, T, Y);
-  else hipLaunchKernelGGL((k_conv3<32, 0>), grid, block, 0, st, in, w, bias, nullptr, out, N, T, Y);
+  if (cin == 16) hipLaunchKernelGGL((k_conv3<16, 0>), grid, block, 0, st, in, w, bias, nullptr, out, N, T, Y,
+                                    bad, nullptr, nullptr);
+  else hipLaunchKernelGGL((k_conv3<32, 0>), grid, block, 0, st, in, w, bias, nullptr, out, N, T, Y, bad, nullptr, nullptr);
   return hipGetLastError();
 }
 
 hipError_t launch_conv_bwd_data(const uint16_t* dpre, const uint16_t* wb, const uint16_t* mask_act, uint16_t* out, int N,
-                                int T, int Y, hipStream_t st) {
+                                int T, int Y, const uint8_t* nz_in, const uint8_t* nz_out, hipStream_t st) {
   hipLaunchKernelGGL((k_conv3<32, 1>), dim3(conv_blocks(N, T, Y)), dim3(kConvWaves * kWave), 0, st, dpre, wb, nullptr,
-                     mask_act, out, N, T, Y);
+                     mask_act, out, N, T, Y, nullptr, nz_in, nz_out);
   return hipGetLastError();
 }
 
 hipError_t launch_conv_wgrad(int cin, const uint16_t* x, const uint16_t* dpre, float* part, float* part_db, float* dw,
-                             float* db, int N, int T, int Y, hipStream_t st) {
+                             float* db, int N, int T, int Y, const uint8_t* nz, hipStream_t st) {
   const int items = wgrad_items(N, Y);
   const dim3 block(kWgWaves * kWave);
-  if (cin == 16) hipLaunchKernelGGL((k_conv3_wgrad<16>), dim3(items), block, 0, st, x, dpre, part, part_db, N, T, Y);
-  else hipLaunchKernelGGL((k_conv3_wgrad<32>), dim3(items), block, 0, st, x, dpre, part, part_db, N, T, Y);
+  if (cin == 16) hipLaunchKernelGGL((k_conv3_wgrad<16>), dim3(items), block, 0, st, x, dpre, part, part_db, N, T, Y, nz);
+  else hipLaunchKernelGGL((k_conv3_wgrad<32>), dim3(items), block, 0, st, x, dpre, part, part_db, N, T, Y, nz);
   const int len = kTaps * kCH * cin;
-  hipLaunchKernelGGL(k_reduce_items, dim3((len + kRedOut - 1) / kRedOut), dim3(kRedOut * kRedPar), 0, st, part, items,
-                     len, dw);
-  hipLaunchKernelGGL(k_reduce_items, dim3(1), dim3(kRedOut * kRedPar), 0, st, part_db, items, kCH, db);
+  hipLaunchKernelGGL(k_reduce_items, dim3((len + kRedOut - 1) / kRedOut + 1), dim3(kRedOut * kRedPar), 0, st, part,
+                     part_db, items, len, dw, db);
   return hipGetLastError();
 }
 
@@ -655,8 +811,7 @@ hipError_t launch_pool(const uint16_t* act, int N, int npos, int centre, uint32_
   const int G = pool_chunks(npos), chunk = (npos + G - 1) / G;
   if (chunk > 0x10000) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_pool_partial, dim3(G, N), dim3(kPoolThreads), 0, st, act, npos, chunk, part);
-  hipLaunchKernelGGL(k_pool_finish, dim3((N * kCH + 255) / 256), dim3(256), 0, st, part, G, chunk, act, N, npos,
-                     centre, h, arg);
+  hipLaunchKernelGGL(k_pool_finish, dim3(N), dim3(kFinPar * kCH), 0, st, part, G, chunk, act, npos, centre, h, arg);
   return hipGetLastError();
 }
 
@@ -669,11 +824,24 @@ hipError_t launch_head(const float* h, const float* labels, int n, const float* 
   return hipGetLastError();
 }
 
+hipError_t launch_row_flags(const int* arg, int N, int T, int Y, int centre, uint32_t* bad, uint8_t* const* nz,
+                            hipStream_t st) {
+  if (T > kWgMaxT) return hipErrorInvalidValue;
+  RowFlags f{{nz[0], nz[1], nz[2], nz[3]}};
+  hipLaunchKernelGGL(k_row_flags, dim3(N), dim3(kFlagThreads), 0, st, arg, T, Y, centre, bad, f);
+  return hipGetLastError();
+}
+
+hipError_t launch_zero_rows(uint16_t* dpre, const uint8_t* nz, int N, int T, int Y, hipStream_t st) {
+  const long long total16 = (long long)N * T * Y * (kXW * kCH / 8);
+  const unsigned grid = (unsigned)std::min<long long>((total16 + 255) / 256, 65536LL);
+  hipLaunchKernelGGL(k_zero_rows, dim3(grid), dim3(256), 0, st, dpre, nz, total16);
+  return hipGetLastError();
+}
+
 hipError_t launch_pool_backward(const float* dh, const int* arg, const uint16_t* act, int N, int npos, int centre,
-                                uint16_t* dpre, hipStream_t st) {
-  const long long total8 = (long long)N * npos * (kCH / 8);
-  const unsigned grid = (unsigned)std::min<long long>((total8 + 255) / 256, 65536LL);
-  hipLaunchKernelGGL(k_pool_backward, dim3(grid), dim3(256), 0, st, dh, arg, act, npos, centre, total8, dpre);
+                                const uint8_t* nz, uint16_t* dpre, hipStream_t st) {
+  hipLaunchKernelGGL(k_pool_backward, dim3(kCH + 1, N), dim3(kRowThreads), 0, st, dh, arg, act, npos, centre, nz, dpre);
   return hipGetLastError();
 }
 

@@ -93,13 +93,19 @@ hipError_t launch_inject_many(void* const* cubes, int dtype, int layout, int n_p
 hipError_t launch_inject_rfi(void* cube, int dtype, int layout, int n_pix, int n_sub, int n_t, int kind, int t0, int len,
                              int s0, float amp, hipStream_t st);
 // classifier kernels (k_cnn.hip)
+// bad[n] is set where sample n has a non-finite pre-activation
 hipError_t launch_conv_fwd(int cin, const uint16_t* in, const uint16_t* w, const float* bias, uint16_t* out, int N,
-                           int T, int Y, hipStream_t st);
+                           int T, int Y, uint32_t* bad, hipStream_t st);
+// nz_in, nz_out: row flags [n][T * Y] of dpre and out (launch_row_flags); unflagged rows are not touched
 hipError_t launch_conv_bwd_data(const uint16_t* dpre, const uint16_t* wb, const uint16_t* mask_act, uint16_t* out, int N,
-                                int T, int Y, hipStream_t st);
+                                int T, int Y, const uint8_t* nz_in, const uint8_t* nz_out, hipStream_t st);
+// Flags of the rows of layers 1..4's pre-activation gradients that may hold nonzeros (nz[0..3]); clears bad
+hipError_t launch_row_flags(const int* arg, int N, int T, int Y, int centre, uint32_t* bad, uint8_t* const* nz,
+                            hipStream_t st);
+hipError_t launch_zero_rows(uint16_t* dpre, const uint8_t* nz, int N, int T, int Y, hipStream_t st);
 int wgrad_items(int N, int Y);   // partial-sum items of the weight-gradient kernel
 hipError_t launch_conv_wgrad(int cin, const uint16_t* x, const uint16_t* dpre, float* part, float* part_db, float* dw,
-                             float* db, int N, int T, int Y, hipStream_t st);
+                             float* db, int N, int T, int Y, const uint8_t* nz, hipStream_t st);
 int pool_chunks(int npos);   // partial keys per sample written by launch_pool (part holds N * this * 32)
 hipError_t launch_pool(const uint16_t* act, int N, int npos, int centre, uint32_t* part, float* h, int* arg,
                        hipStream_t st);
@@ -107,7 +113,7 @@ hipError_t launch_pool(const uint16_t* act, int N, int npos, int centre, uint32_
 hipError_t launch_head(const float* h, const float* labels, int n, const float* th, float* hs, float* gh, float* dh,
                        float* logits, float* prob, float* loss, int backward, hipStream_t st);
 hipError_t launch_pool_backward(const float* dh, const int* arg, const uint16_t* act, int N, int npos, int centre,
-                                uint16_t* dpre, hipStream_t st);
+                                const uint8_t* nz, uint16_t* dpre, hipStream_t st);
 hipError_t launch_adam(float* th, float* m, float* v, const float* g, int n, float lr, float b1, float b2, float eps,
                        float bc1, float bc2, hipStream_t st);
 hipError_t launch_prep_weights(const float* wsrc, int cin, uint16_t* wf, uint16_t* wb, hipStream_t st);
