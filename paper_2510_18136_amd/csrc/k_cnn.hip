@@ -228,6 +228,131 @@ __global__ __launch_bounds__(kConvWaves * kWave) void k_conv3(const uint16_t* __
   if (MODE == 0 && nf != 0.0f) bad[n] = 1u;
 }
 
+// ------------------------------------------------- forward, four rows a wave
+// The forward convolution for images of many rows. With one output row per wave
+// every MFMA takes its 1 KB of weights and 1 KB of inputs from LDS, 9.3 of the
+// LDS's cycles per MFMA against the 8 the four matrix cores need. Here a wave
+// keeps all weights in registers (27 x CIN / 16 operands of 4 registers; one
+// wave per SIMD has 512) and computes four rows, so each staged input row is
+// read once for the up to three rows it feeds: 0.5 KB per MFMA, and no LDS for
+// weights, which leaves room for planes of 18 rows. Per output the K steps run
+// in the order of k_conv3 (dt, dy, dx, channel half), so results are bitwise
+// those of k_conv3.
+constexpr int kRowsWaves = 4, kRowsPer = 4;
+constexpr int kRowsYT = kRowsWaves * kRowsPer;     // output rows per plane per workgroup
+constexpr int kRowsRY = kRowsYT + 2;
+typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+template <int CIN>
+__global__ __launch_bounds__(kRowsWaves * kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_conv3_rows(
+    const uint16_t* __restrict__ in, const uint16_t* __restrict__ wm, const float* __restrict__ bias,
+    uint16_t* __restrict__ out, int T, int Y, int TT, uint32_t* __restrict__ bad) {
+  constexpr int G8 = CIN / 8, KB = CIN / 16, NB = 3 * KB;      // NB: K steps per (dt, dy)
+  constexpr int ROW = kConvXS * G8, SLOT = kRowsRY * ROW;
+  constexpr int PLANE = kRowsRY * kXW * G8, NT = kRowsWaves * kWave, PER = (PLANE + NT - 1) / NT;
+  __shared__ uint4 xl[4 * SLOT];
+  const int n_yb = (Y + kRowsYT - 1) / kRowsYT, n_tb = (T + TT - 1) / TT;
+  const int tb = blockIdx.x % n_tb, yb = (blockIdx.x / n_tb) % n_yb, n = blockIdx.x / (n_tb * n_yb);
+  const int y0 = yb * kRowsYT, t0 = tb * TT, t1 = min(t0 + TT, T);
+  const int tid = threadIdx.x, l = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  v8bf wa[9 * NB];
+#pragma unroll
+  for (int s = 0; s < 9 * NB; ++s) wa[s] = reinterpret_cast<const v8bf*>(wm)[s * kWave + l];
+  for (int i = tid; i < 4 * kRowsRY * 2 * G8; i += NT) {           // x halo of every slot and row
+    const int c = i % G8, side = (i / G8) % 2, r = i / (2 * G8);
+    xl[r * ROW + (side ? kConvXS - 1 : 0) * G8 + c] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  auto fetch = [&](int tp, uint4 (&v)[PER]) {
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int i = tid + q * NT;
+      const int c = i % G8, x = (i / G8) % kXW, ry = i / (G8 * kXW), y = y0 - 1 + ry;
+      const bool ok = (PLANE % NT == 0 || i < PLANE) && tp >= 0 && tp < T && y >= 0 && y < Y;
+      v[q] = ok ? reinterpret_cast<const uint4*>(in + ((((size_t)n * T + tp) * Y + y) * kXW + x) * CIN)[c]
+                : make_uint4(0u, 0u, 0u, 0u);
+    }
+  };
+  auto stage = [&](int tp, const uint4 (&v)[PER]) {
+    uint4* sl = xl + ((tp + 4) & 3) * SLOT;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int i = tid + q * NT;
+      if (PLANE % NT == 0 || i < PLANE) {
+        const int c = i % G8, x = (i / G8) % kXW, ry = i / (G8 * kXW), xs = x + 1;
+        sl[ry * ROW + xs * G8 + (c ^ conv_swz<CIN>(xs))] = v[q];
+      }
+    }
+  };
+  for (int tp = t0 - 1; tp <= t0 + 1; ++tp) {
+    uint4 v[PER];
+    fetch(tp, v);
+    stage(tp, v);
+  }
+  __syncthreads();
+
+  const int x = l & 31, half = l >> 5;
+  int off[NB];                               // 16-byte chunk of K step h within a staged row
+#pragma unroll
+  for (int h = 0; h < NB; ++h) {
+    const int dx = h / KB, kb = h % KB;
+    off[h] = (x + dx) * G8 + ((2 * kb) ^ (half ^ conv_swz<CIN>(x + dx)));
+  }
+  float bv[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) bv[i] = bias[8 * (i / 4) + 4 * half + i % 4];
+  const int yw = y0 + kRowsPer * w;
+  float nf = 0.0f;                           // 0 unless some pre-activation is infinite or NaN
+  for (int t = t0; t < t1; ++t) {
+    uint4 v[PER];
+    fetch(t + 2, v);
+    if (yw < Y) {
+      v16f acc[kRowsPer] = {};
+#pragma unroll
+      for (int dt = 0; dt < 3; ++dt) {
+        const uint4* base = xl + ((t + 3 + dt) & 3) * SLOT + kRowsPer * w * ROW;
+#pragma unroll
+        for (int ri = 0; ri < kRowsPer + 2; ++ri) {
+          v8bf b[NB];
+#pragma unroll
+          for (int h = 0; h < NB; ++h) __builtin_memcpy(&b[h], base + ri * ROW + off[h], 16);
+#pragma unroll
+          for (int h = 0; h < NB; ++h)
+#pragma unroll
+            for (int r = 0; r < kRowsPer; ++r) {
+              const int dy = ri - r;
+              if (dy >= 0 && dy < 3)
+                acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[(dt * 3 + dy) * NB + h], b[h], acc[r], 0, 0, 0);
+            }
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < kRowsPer; ++r) {
+        if (yw + r >= Y) break;
+        uint16_t* po = out + ((((size_t)n * T + t) * Y + yw + r) * kXW + x) * kCH + 4 * half;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          v4f u;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            u[j] = acc[r][4 * g + j] + bv[4 * g + j];
+            nf = __builtin_fmaf(u[j], 0.0f, nf);
+            u[j] = fmaxf(u[j], 0.0f);
+          }
+          const v4bf o = __builtin_convertvector(u, v4bf);
+          uint2 pk;
+          __builtin_memcpy(&pk, &o, 8);
+          *reinterpret_cast<uint2*>(po + 8 * g) = pk;
+        }
+      }
+    }
+    stage(t + 2, v);                         // slot of plane t - 2, which step t does not read
+    __syncthreads();
+  }
+  if (nf != 0.0f) bad[n] = 1u;
+}
+
 // --------------------------------------------------------- weight gradient
 // dW[co][tap][ci] = sum over positions of dpre[p][co] * in[p + offset(tap)][ci]
 // and db[co] = sum of dpre[p][co]: per tap a GEMM with M = 32 output channels,
@@ -778,6 +903,17 @@ static unsigned conv_blocks(int N, int T, int Y) {
 
 hipError_t launch_conv_fwd(int cin, const uint16_t* in, const uint16_t* w, const float* bias, uint16_t* out, int N,
                            int T, int Y, uint32_t* bad, hipStream_t st) {
+  // four rows a wave unless that leaves a quarter or more of the rows computed idle
+  if (4 * ((Y + kRowsYT - 1) / kRowsYT) * kRowsYT < 5 * ((Y + kConvYT - 1) / kConvYT) * kConvYT) {
+    // planes per workgroup: more share the two halo planes, fewer fill the chip
+    int TT = kConvTT;
+    auto blocks = [&](int tt) { return (unsigned)N * ((Y + kRowsYT - 1) / kRowsYT) * ((T + tt - 1) / tt); };
+    while (TT > 4 && blocks(TT) < 256) TT /= 2;
+    const dim3 g(blocks(TT)), b(kRowsWaves * kWave);
+    if (cin == 16) hipLaunchKernelGGL((k_conv3_rows<16>), g, b, 0, st, in, w, bias, out, T, Y, TT, bad);
+    else hipLaunchKernelGGL((k_conv3_rows<32>), g, b, 0, st, in, w, bias, out, T, Y, TT, bad);
+    return hipGetLastError();
+  }
   const dim3 grid(conv_blocks(N, T, Y)), block(kConvWaves * kWave);
   if (cin == 16) hipLaunchKernelGGL((k_conv3<16, 0>), grid, block, 0, st, in, w, bias, nullptr, out, N, T, Y,
                                     bad, nullptr, nullptr);
