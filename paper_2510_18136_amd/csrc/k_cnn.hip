@@ -186,16 +186,19 @@ __global__ __launch_bounds__(kConvWaves * kWave) void k_conv3(const uint16_t* __
       for (int g = 0; g < 9; ++g) {
         const int dt = g / 3, dy = g % 3;
         if (MODE == 1 && !(rows_of(t - 1 + dt) >> (w + dy) & 1)) continue;
+        // a group's reads go out together: left to itself the compiler waits out
+        // each one before its MFMA
+        v8bf a[S / 9], b[S / 9];
 #pragma unroll
         for (int h = 0; h < S / 9; ++h) {
-          const int s = g * (S / 9) + h;                       // K step: tap, then half of the input channels
-          const int dx = h / (CIN / 16), kb = h % (CIN / 16);
+          const int dx = h / (CIN / 16), kb = h % (CIN / 16);  // K step g (S / 9) + h: tap, then half of the input channels
           const uint4* rowp = xl + ((t - 1 + dt + 4) & 3) * SLOT + (w + dy) * ROW + (x + dx) * G8;
-          const uint4 bv = rowp[(2 * kb) ^ hs[dx]];
-          v8bf b;
-          __builtin_memcpy(&b, &bv, 16);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[s * kWave], b, acc, 0, 0, 0);
+          a[h] = wa[(g * (S / 9) + h) * kWave];
+          __builtin_memcpy(&b[h], rowp + ((2 * kb) ^ hs[dx]), 16);
         }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < S / 9; ++h) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[h], b[h], acc, 0, 0, 0);
       }
       const size_t pos = (((size_t)n * T + t) * Y + y) * kXW + x;
 #pragma unroll
@@ -307,26 +310,39 @@ __global__ __launch_bounds__(kRowsWaves * kWave) __attribute__((amdgpu_waves_per
   for (int t = t0; t < t1; ++t) {
     uint4 v[PER];
     fetch(t + 2, v);
+    v16f acc[kRowsPer] = {};
     if (yw < Y) {
-      v16f acc[kRowsPer] = {};
+      // 18 steps (dt, input row), the next one's reads in flight during each (left
+      // to itself the compiler waited out every read: 251 us a layer)
+      constexpr int STEPS = 3 * (kRowsPer + 2);
+      v8bf b[2][NB];
+      auto read_row = [&](int k, v8bf (&d)[NB]) {
+        const uint4* base = xl + ((t + 3 + k / (kRowsPer + 2)) & 3) * SLOT + (kRowsPer * w + k % (kRowsPer + 2)) * ROW;
 #pragma unroll
-      for (int dt = 0; dt < 3; ++dt) {
-        const uint4* base = xl + ((t + 3 + dt) & 3) * SLOT + kRowsPer * w * ROW;
+        for (int h = 0; h < NB; ++h) __builtin_memcpy(&d[h], base + off[h], 16);
+      };
+      read_row(0, b[0]);
 #pragma unroll
-        for (int ri = 0; ri < kRowsPer + 2; ++ri) {
-          v8bf b[NB];
+      for (int k = 0; k < STEPS; ++k) {
+        const int dt = k / (kRowsPer + 2), ri = k % (kRowsPer + 2);
+        if (k + 1 < STEPS) read_row(k + 1, b[(k + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int h = 0; h < NB; ++h) __builtin_memcpy(&b[h], base + ri * ROW + off[h], 16);
+        for (int h = 0; h < NB; ++h)
 #pragma unroll
-          for (int h = 0; h < NB; ++h)
-#pragma unroll
-            for (int r = 0; r < kRowsPer; ++r) {
-              const int dy = ri - r;
-              if (dy >= 0 && dy < 3)
-                acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[(dt * 3 + dy) * NB + h], b[h], acc[r], 0, 0, 0);
-            }
-        }
+          for (int r = 0; r < kRowsPer; ++r) {
+            const int dy = ri - r;
+            if (dy >= 0 && dy < 3)
+              acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[(dt * 3 + dy) * NB + h], b[k & 1][h], acc[r], 0, 0, 0);
+          }
+        __builtin_amdgcn_sched_barrier(0);
       }
+    }
+    // staged before the outputs are stored: a wait for the loads would otherwise
+    // be one for the stores too
+    stage(t + 2, v);                         // slot of plane t - 2, which step t does not read
+    __syncthreads();
+    if (yw < Y) {
 #pragma unroll
       for (int r = 0; r < kRowsPer; ++r) {
         if (yw + r >= Y) break;
@@ -347,8 +363,6 @@ __global__ __launch_bounds__(kRowsWaves * kWave) __attribute__((amdgpu_waves_per
         }
       }
     }
-    stage(t + 2, v);                         // slot of plane t - 2, which step t does not read
-    __syncthreads();
   }
   if (nf != 0.0f) bad[n] = 1u;
 }
@@ -500,18 +514,20 @@ __global__ __launch_bounds__(kWgWaves * kWave) void k_conv3_wgrad(const uint16_t
 #pragma unroll
     for (int r = 0; r < kWgR; ++r) {
       if (!(now >> r & 1)) continue;
+      v8bf a[2][3], b[2] = {};                 // (a row's reads go out together, ahead of its MFMAs)
 #pragma unroll
       for (int xh = 0; xh < 2; ++xh) {
         const int xo = 16 * xh + 8 * h;
-        v8bf b = {};
-        if (col < CIN) __builtin_memcpy(&b, sb + (r + dy) * CIN * kWgXP + xo, 16);
+        if (col < CIN) __builtin_memcpy(&b[xh], sb + (r + dy) * CIN * kWgXP + xo, 16);
 #pragma unroll
-        for (int ddx = 0; ddx < 3; ++ddx) {
-          v8bf a;
-          __builtin_memcpy(&a, sa + ddx * DCOPY + r * kXW + xo, 16);
-          acc[ddx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[ddx], 0, 0, 0);
-        }
+        for (int ddx = 0; ddx < 3; ++ddx) __builtin_memcpy(&a[xh][ddx], sa + ddx * DCOPY + r * kXW + xo, 16);
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int xh = 0; xh < 2; ++xh)
+#pragma unroll
+        for (int ddx = 0; ddx < 3; ++ddx)
+          acc[ddx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[xh][ddx], b[xh], acc[ddx], 0, 0, 0);
     }
     if (more) stage_in(t + 2, vin);  // ring slot of plane t - 2, not read at step t
     stage_d(t + 1, vd);              // the other dT buffer
