@@ -890,27 +890,65 @@ struct CutoutDesc {
   int px, py, dm, toa;
 };
 
+// The series run along t in the cube and along s in the cutout, so a workgroup
+// takes 8 pixels x 16 sub-bands x 64 times through the LDS: a wave reads 64 times
+// of a series at once (a sub-band pair at a time, 32 loads in flight a lane) and
+// stores 8 pixels' samples of one time (256 bytes). Row pitch 65 words: the pairs
+// a wave writes down a column fall in distinct banks, and so do the words it
+// reads along a row. Bound by memory traffic: 64 cutouts of 64 x 32 x 32 x 16
+// from FP16 cubes (134 MB read and as much written) take 54 us, 5.0 TB/s; with a
+// thread per output sample, whose wave's loads touched 64 lines, 268.
+constexpr int kCutX = 8, kCutS = 16, kCutT = 64, kCutWaves = 4;
+typedef uint32_t u32_a2 __attribute__((aligned(2)));      // the output is aligned to a sample only
 template <typename ST>
-__global__ void k_cutouts(const ST* const* __restrict__ cubes, const CutoutDesc* __restrict__ desc,
-                          const int* __restrict__ delays, int nx, int ny, int n_sub, int n_t, int ct,
-                          uint16_t* __restrict__ out, long long total) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int s = (int)(i % n_sub);
-    long long r = i / n_sub;
-    const int x = (int)(r % kXW); r /= kXW;
-    const int y = (int)(r % kXW); r /= kXW;
-    const int tt = (int)(r % ct);
-    const int k = (int)(r / ct);
-    const CutoutDesc d = desc[k];
-    const int xi = d.px + x - kXW / 2, yi = d.py + y - kXW / 2;
-    const int t = d.toa - ct / 2 + tt + delays[d.dm * n_sub + s];
-    float v = 0.f;
-    if (xi >= 0 && xi < nx && yi >= 0 && yi < ny && t >= 0 && t < n_t)
-      v = to_f32(cubes[d.cube][((size_t)(yi * nx + xi) * n_sub + s) * n_t + t]);
-    out[i] = f2bf(v);
+__global__ __launch_bounds__(kCutWaves * kWave) void k_cutouts(
+    const ST* const* __restrict__ cubes, const CutoutDesc* __restrict__ desc, const int* __restrict__ delays, int nx,
+    int ny, int n_t, int ct, uint16_t* __restrict__ out) {
+  constexpr int kWords = kCutX * kCutS / 2, kPairs = kWords / kCutWaves;   // words of a time; sub-band pairs of a wave
+  constexpr int kPitch = kWords + 1;
+  __shared__ uint32_t tile[kCutT * kPitch];
+  const int xg = blockIdx.x % (kXW / kCutX), y = blockIdx.x / (kXW / kCutX) % kXW, k = blockIdx.x / (kXW / kCutX * kXW);
+  const int tt0 = blockIdx.y * kCutT;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), l = threadIdx.x % kWave;
+  const CutoutDesc d = desc[k];
+  const ST* cube = cubes[d.cube];
+  const int yi = d.py + y - kXW / 2;
+  const int t0 = d.toa - ct / 2 + tt0 + l;
+  ST v[kPairs][2];
+#pragma unroll
+  for (int i = 0; i < kPairs; ++i) {
+    const int word = w * kPairs + i, s = 2 * (word % (kCutS / 2));
+    const int xi = d.px + xg * kCutX + word / (kCutS / 2) - kXW / 2;
+    const bool inside = xi >= 0 && xi < nx && yi >= 0 && yi < ny;
+    // outside the image or the series: any sample of the cube, dropped below
+    const ST* row = cube + (inside ? ((size_t)(yi * nx + xi) * kCutS + s) * n_t : 0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int t = t0 + delays[d.dm * kCutS + s + h];
+      v[i][h] = row[(inside ? (size_t)h * n_t : 0) + min(max(t, 0), n_t - 1)];
+    }
   }
+#pragma unroll
+  for (int i = 0; i < kPairs; ++i) {
+    const int word = w * kPairs + i, s = 2 * (word % (kCutS / 2));
+    const int xi = d.px + xg * kCutX + word / (kCutS / 2) - kXW / 2;
+    const bool inside = xi >= 0 && xi < nx && yi >= 0 && yi < ny;
+    uint32_t pair = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int t = t0 + delays[d.dm * kCutS + s + h];
+      const float f = inside && t >= 0 && t < n_t ? to_f32(v[i][h]) : 0.f;
+      pair |= (uint32_t)f2bf(f) << (16 * h);
+    }
+    tile[l * kPitch + word] = pair;
+  }
+  __syncthreads();
+  u32_a2* o = (u32_a2*)out + (((size_t)k * ct + tt0) * kXW + y) * (kXW * kCutS / 2) + xg * kWords + l;
+  const int n = min(kCutT, ct - tt0);
+#pragma unroll 8
+  for (int tt = w; tt < n; tt += kCutWaves) o[(size_t)tt * (kXW * kXW * kCutS / 2)] = tile[tt * kPitch + l];
 }
+static_assert(kCutX * kCutS / 2 == kWave && kCutT == kWave, "one lane per word and per time");
 
 // --------------------------------------------------------------- launchers
 static unsigned conv_blocks(int N, int T, int Y) {
@@ -1011,18 +1049,15 @@ hipError_t launch_prep_weights(const float* wsrc, int cin, uint16_t* wf, uint16_
 
 hipError_t launch_cutouts(int store_dtype, const void* const* cubes, const void* desc, const int* delays, int n_cut,
                           int nx, int ny, int n_sub, int n_t, int ct, uint16_t* out, hipStream_t st) {
-  const long long total = (long long)n_cut * ct * kXW * kXW * n_sub;
-  const unsigned grid = (unsigned)std::min<long long>((total + 255) / 256, 65536LL * 4);
+  if (n_sub != kCutS) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)n_cut * kXW * (kXW / kCutX), (ct + kCutT - 1) / kCutT), block(kCutWaves * kWave);
   const CutoutDesc* d = (const CutoutDesc*)desc;
   if (store_dtype == DT_F32)
-    hipLaunchKernelGGL(k_cutouts<float>, dim3(grid), dim3(256), 0, st, (const float* const*)cubes, d, delays, nx, ny,
-                       n_sub, n_t, ct, out, total);
+    hipLaunchKernelGGL(k_cutouts<float>, grid, block, 0, st, (const float* const*)cubes, d, delays, nx, ny, n_t, ct, out);
   else if (store_dtype == DT_F16)
-    hipLaunchKernelGGL(k_cutouts<_Float16>, dim3(grid), dim3(256), 0, st, (const _Float16* const*)cubes, d, delays, nx,
-                       ny, n_sub, n_t, ct, out, total);
+    hipLaunchKernelGGL(k_cutouts<_Float16>, grid, block, 0, st, (const _Float16* const*)cubes, d, delays, nx, ny, n_t, ct, out);
   else
-    hipLaunchKernelGGL(k_cutouts<bf16_t>, dim3(grid), dim3(256), 0, st, (const bf16_t* const*)cubes, d, delays, nx, ny,
-                       n_sub, n_t, ct, out, total);
+    hipLaunchKernelGGL(k_cutouts<bf16_t>, grid, block, 0, st, (const bf16_t* const*)cubes, d, delays, nx, ny, n_t, ct, out);
   return hipGetLastError();
 }
 
