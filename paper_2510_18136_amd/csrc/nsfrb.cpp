@@ -1110,7 +1110,7 @@ static nsfrb_status run_impl(nsfrb_search* h, const void* d_cube, int t_start, v
   if (c.layout == NSFRB_LAYOUT_TSP) {
     StatsLaunch sa{d_cube, c.n_time, c.n_sub, h->n_pix, c.norm, c.in_dtype, c.store_dtype,
                    h->d_ext_med, h->d_ext_sig, h->d_med, h->d_sig, h->d_z, h->d_flags, t_start};
-    HIP_TRY(launch_stats(sa, st));
+    HIP_TRY(launch_stats(&sa, 1, st));
     z = h->d_z;
   }
   h->last_z = z;
@@ -1530,18 +1530,20 @@ extern "C" nsfrb_status nsfrb_batch_use_graph(nsfrb_batch* b, int32_t on) {
 
 // Statistics of every cube (or flag reset for search-layout input); sets last_z.
 static nsfrb_status batch_stats(nsfrb_batch* b, const void* const* d_cubes, hipStream_t st) {
+  std::vector<StatsLaunch> stats;
+  stats.reserve(b->cubes.size());
   for (size_t i = 0; i < b->cubes.size(); ++i) {
     nsfrb_search* h = b->cubes[i];
     const nsfrb_search_config& c = h->cfg;
     if (c.layout == NSFRB_LAYOUT_TSP) {
-      StatsLaunch sa{d_cubes[i], c.n_time, c.n_sub, h->n_pix, c.norm, c.in_dtype, c.store_dtype,
-                     h->d_ext_med, h->d_ext_sig, h->d_med, h->d_sig, h->d_z, h->d_flags};
-      HIP_TRY(launch_stats(sa, st));
+      stats.push_back({d_cubes[i], c.n_time, c.n_sub, h->n_pix, c.norm, c.in_dtype, c.store_dtype,
+                       h->d_ext_med, h->d_ext_sig, h->d_med, h->d_sig, h->d_z, h->d_flags});
       h->last_z = h->d_z;
     } else {
       h->last_z = d_cubes[i];
     }
   }
+  HIP_TRY(launch_stats(stats.data(), (int)stats.size(), st));
   return NSFRB_OK;
 }
 

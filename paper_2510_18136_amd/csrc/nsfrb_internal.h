@@ -19,7 +19,8 @@ struct StatsLaunch {
   unsigned long long* flag_count;
   int t_start = 0;   // time index of the oldest sample when x is a ring of n_t samples (0: plain cube)
 };
-hipError_t launch_stats(const StatsLaunch& a, hipStream_t st);
+// Statistics of n cubes; neighbours of one shape share a launch.
+hipError_t launch_stats(const StatsLaunch* a, int n, hipStream_t st);
 hipError_t launch_zero_u64(unsigned long long* p, hipStream_t st);
 
 // One cube's candidate list. keys, count and flags are device memory, out and
