@@ -135,13 +135,16 @@ __device__ __forceinline__ void cand_top(const CandDesc& d, int blk) {
   int n = fill, total = hits;                                 // keys to rank, pixels at or above the threshold
   if (d.blocks > 1) {
     for (int i = tid; i < n; i += kTopThreads) d.keys[(size_t)blk * K + i] = s[i];
-    if (tid == 0) d.count[2 + blk] = n;
-    __syncthreads();
     if (tid == 0) {
+      d.count[2 + blk] = n;
       atomicAdd(&d.count[0], hits);
-      __threadfence();                                        // keys and counts before the ticket
-      last = atomicAdd(&d.count[1], 1) == d.blocks - 1;
     }
+    // keys and counts before the ticket: every wave writes back and waits for its
+    // own stores (a barrier alone does not wait for stores, and the workgroup that
+    // merges may sit on another XCD, behind another L2)
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) last = atomicAdd(&d.count[1], 1) == d.blocks - 1;
     __syncthreads();
     if (!last) return;
     __threadfence();                                          // the others' keys after it
