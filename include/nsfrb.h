@@ -23,6 +23,9 @@
  *     copies what it keeps. Device pointers stay owned by the caller.
  *   - `stream` is a hipStream_t passed as void*; NULL means the default stream.
  *   - A handle is not thread-safe; distinct handles are independent.
+ *   - The runs of one handle share its buffers and must not overlap on the
+ *     GPU: enqueue them on one stream, or order the streams. Runs that do
+ *     overlap have undefined results; runs after them are unaffected.
  *
  * Cube layout: element (t, s, p) of a raw cube is at index
  *   (t * n_sub + s) * (nx * ny) + p,  with pixel p = y * nx + x,

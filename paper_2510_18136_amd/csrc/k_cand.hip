@@ -144,13 +144,16 @@ __device__ __forceinline__ void cand_top(const CandDesc& d, int blk) {
     // merges may sit on another XCD, behind another L2)
     __threadfence();
     __syncthreads();
-    if (tid == 0) last = atomicAdd(&d.count[1], 1) == d.blocks - 1;
+    // (the last ticket wraps the counter to 0 by itself: should the runs of one
+    // handle ever overlap, no reset loses the other's tickets, and the next run
+    // starts from 0 again)
+    if (tid == 0) last = atomicInc((unsigned*)&d.count[1], (unsigned)d.blocks - 1) == (unsigned)d.blocks - 1;
     __syncthreads();
     if (!last) return;
     __threadfence();                                          // the others' keys after it
     // merge: at most kTopMerge keys, thread t holding every kTopThreads-th
     constexpr int PM = kTopMerge / kTopThreads;
-    total = __hip_atomic_load(&d.count[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) total = atomicExch(&d.count[0], 0);         // (only this thread reports it)
     unsigned long long k64[PM];
     uint32_t k32[PM];
     n = 0;
@@ -173,15 +176,14 @@ __device__ __forceinline__ void cand_top(const CandDesc& d, int blk) {
       if (k32[i] >= Tm) s[atomicAdd(&fill, 1)] = k64[i];
     __syncthreads();
     n = fill;                                                 // K, or more if the K-th is tied
-    if (tid < 2) d.count[tid] = 0;                            // ready for the next run
   }
   const int kept = n < K ? n : K;
   for (int r = tid; r < n; r += kTopThreads) {
     const unsigned long long k = s[r];
     int rank = 0;
     for (int q = 0; q < n; ++q) rank += s[q] > k;
-    if (rank >= K) continue;
     const int p = (int)(0xffffffffu - (uint32_t)(k & 0xffffffffull));
+    if (rank >= K || (uint32_t)p >= (uint32_t)d.n_pix) continue;   // (every key names a pixel, unless runs overlap)
     nsfrb_candidate c;
     c.x = p % d.nx;
     c.y = p / d.nx;
@@ -194,8 +196,7 @@ __device__ __forceinline__ void cand_top(const CandDesc& d, int blk) {
   if (tid == 0) {
     d.n_out[0] = kept;
     d.n_out[1] = total;
-    *(unsigned long long*)(d.n_out + 2) = *d.flags;
-    *d.flags = 0ull;
+    *(unsigned long long*)(d.n_out + 2) = atomicExch(d.flags, 0ull);
   }
 }
 
@@ -324,8 +325,7 @@ __global__ __launch_bounds__(kSelThreads) void k_cand_select(
   if (threadIdx.x == 0) {
     n_out[0] = K;
     n_out[1] = n;
-    *(unsigned long long*)(n_out + 2) = *flags;
-    *flags = 0ull;
+    *(unsigned long long*)(n_out + 2) = atomicExch(flags, 0ull);
   }
 }
 

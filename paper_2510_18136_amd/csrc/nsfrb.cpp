@@ -687,7 +687,7 @@ struct nsfrb_search {
   unsigned long long* d_keys = nullptr;
   int32_t* d_count = nullptr;
   unsigned long long* d_flags = nullptr;   // zero between runs
-  bool flags_dirty = false;                // a run was cut short between its statistics and its candidate list
+  bool dirty = false;                      // a run was cut short: d_flags and the counters of d_count may not be zero
   // pinned host memory the candidate kernels write
   nsfrb_candidate* h_cands = nullptr;
   int32_t* h_nout = nullptr;               // records, total, flagged (64 bits)
@@ -1084,8 +1084,11 @@ static CandDesc cand_desc(const nsfrb_search* h) {
 // Before a run's first launch: the counters its kernels add to are zero unless
 // the last run failed half-way.
 static nsfrb_status begin_run(nsfrb_search* h, hipStream_t st) {
-  if (h->flags_dirty) HIP_TRY(launch_zero_u64(h->d_flags, st));
-  h->flags_dirty = true;
+  if (h->dirty) {
+    HIP_TRY(launch_zero_u64(h->d_flags, st));
+    HIP_TRY(launch_zero_u64((unsigned long long*)h->d_count, st));   // its two counters
+  }
+  h->dirty = true;
   return NSFRB_OK;
 }
 
@@ -1119,7 +1122,7 @@ static nsfrb_status run_impl(nsfrb_search* h, const void* d_cube, int t_start, v
   if (s2 != NSFRB_OK) return s2;
   if (h->profiling) HIP_TRY(hipEventRecord(h->ev[2], st));
   HIP_TRY(launch_candidates(cand_desc(h), st));
-  h->flags_dirty = false;
+  h->dirty = false;
   if (h->profiling) HIP_TRY(hipEventRecord(h->ev[3], st));
   HIP_TRY(hipEventRecord(h->done, st));
   h->ran = true;
@@ -1567,7 +1570,7 @@ static nsfrb_status batch_begin(nsfrb_batch* b, hipStream_t st) {
 static void batch_done(nsfrb_batch* b) {
   for (auto* h : b->cubes) {
     h->ran = true;
-    h->flags_dirty = false;
+    h->dirty = false;
   }
   b->ran = true;
 }

@@ -90,3 +90,24 @@ def test_batch_lists():
             for i, (nx, ny) in enumerate(shapes):
                 recs, total = b.candidates(i)
                 assert ([(r["x"], r["y"], r["snr"]) for r in recs], total) == expected(vs[i], 1.0, 12, nx)
+
+
+def test_runs_after_overlapping_ones():
+    """Runs that overlap on two streams spoil each other only: the counters of the next run start at zero."""
+    v = values("distinct", 256 * 256, np.random.default_rng(2))
+    flagged = np.array([5, 9000, 65535])
+    want = v.copy()
+    want[flagged] = 0.0                                    # a flagged sample is searched as 0
+    v[flagged] = np.nan
+    x = torch.from_numpy(v).cuda()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    with nsfrb.Search(config(256, 256, 16, -50.0)) as s:
+        print("[gpu] candidates, overlapping runs", flush=True)
+        for _ in range(3):
+            for st in streams * 8:
+                s.run(x.data_ptr(), st.cuda_stream)
+            torch.cuda.synchronize()
+            s.run(x.data_ptr(), streams[0].cuda_stream)
+            assert got(s) == expected(want, -50.0, 16, 256)
+            assert s.flag_count() == flagged.size
