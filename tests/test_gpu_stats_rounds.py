@@ -91,3 +91,43 @@ def values(kind, nt, shape, rng):
 def test_value_distributions(kind, nt):
     rng = np.random.default_rng(nt)
     check(values(kind, nt, (nt, 2, 48), rng), 8, 6)
+
+
+def edge_series(n, edge):
+    """64 series [64][n] whose MAD rank lies at the edge of a crowded bin of distances.
+
+    The median is 1 + 2^-24, halfway between two FP32 values, and distances are taken from the FP32 value 1: a
+    sample below has an FP64 distance 2^-24 more than its key, one above 2^-24 less. Around the edge lie a key 2^-24
+    short of 0.3 from below the median and the key 0.3 from above it, whose order the FP64 distances reverse. The
+    outlier, which sets the bins, sweeps 64 consecutive FP32 values, so that a bin's edge falls between the two keys
+    for some of them.
+    """
+    u, half, rng = 2.0 ** -24, n // 2, np.random.default_rng(n)
+    key = round(0.3 / (2 * u)) * 2 * u
+
+    def below(m, lo, hi):
+        return 1.0 - np.round(rng.uniform(lo, hi, m) / u) * u
+
+    def above(m, lo, hi):
+        return 1.0 + np.round(rng.uniform(lo, hi, m) / (2 * u)) * 2 * u
+
+    if edge == "lower":                       # the first key of bin 1
+        q, far = half - n // 8, np.float32(key * 1020 / 3.5)
+        x = [[1.0, 1.0 - (key - u)], below(q - 2, 0.01, 0.25), below(n // 8, key + 0.01, key + 0.2),
+             [1.0 + 2 * u], above(n // 8 - 2, 0.01, 0.25), [1.0 + key], above(half - n // 8 - 1, key + 0.01, key + 0.2)]
+    else:                                     # the last key of bin 1
+        q, far = n // 16 + n // 4, np.float32(key * 1020 / 7.5)
+        x = [[1.0], below(n // 16 - 1, 0.01, 0.12), below(n // 4 - 1, 0.16, 0.28), [1.0 - (key - u)],
+             below(half - q, 0.31, 0.5), [1.0 + 2 * u], above(half - q, 0.16, 0.28), [1.0 + key],
+             above(q - 3, 0.31, 0.5)]
+    outlier = 1.0 + (np.float64(far) + (np.arange(64) - 32) * np.float64(np.spacing(far)))
+    return np.concatenate([np.repeat(np.concatenate(x)[None], 64, 0), outlier[:, None]], axis=1)
+
+
+@pytest.mark.parametrize("nt", [256, 512, 1024, 2048, 4096])
+@pytest.mark.parametrize("edge", ["lower", "upper"])
+def test_rank_at_the_edge_of_a_crowded_bin(nt, edge):
+    x = edge_series(nt, edge)
+    assert x.shape == (64, nt) and (x == x.astype(np.float32)).all()
+    assert (np.median(x, axis=1) == 1.0 + 2.0 ** -24).all()
+    check(x.T[:, None], 8, 8)
