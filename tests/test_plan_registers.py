@@ -1,0 +1,60 @@
+"""Registers and row reads of compiled search plans (no GPU needed).
+
+Plans are compiled for gfx950 as a program that has imported PyTorch compiles
+them, and read back: a register too many costs a workgroup per CU, a spill a
+kernel form or a whole batch, and none of it shows in results.
+"""
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+from tests._lib import ensure_built
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LLVM = "/opt/rocm/llvm/bin/"
+W5 = [1, 2, 4, 8, 16]
+W8 = W5 + [32, 64, 100]
+W12 = W5 + [32, 64, 128, 256, 512, 1024, 1200]
+W13 = [1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 100]
+
+COMPILE = """
+import sys; sys.path.insert(0, %r)
+import torch, numpy as np
+from paper_2510_18136_amd import nsfrb
+nsfrb.SearchConfig(64, 64, {nt}, np.linspace(1.311, 1.499, {ns}), np.linspace(0, 4000, {n_dm}), {widths},
+                   in_dtype={store!r}, store_dtype={store!r}).plan_source(compile=True)
+""" % ROOT
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    ensure_built()
+
+
+def compiled(path, lean=0, max_acc=3, **plan):
+    """Code object of a plan, compiled in a child process."""
+    env = dict(os.environ, NSFRB_DUMP_CODE=str(path), NSFRB_DEBUG_LEAN=str(lean), NSFRB_DEBUG_MAX_ACC=str(max_acc))
+    subprocess.run([sys.executable, "-c", COMPILE.format(**plan)], check=True, env=env, timeout=300)
+    return str(path)
+
+
+def registers(code):
+    """{kernel: (VGPRs, bytes of scratch a lane)}"""
+    notes = subprocess.run([LLVM + "llvm-readelf", "--notes", code], capture_output=True, text=True, check=True).stdout
+    out = {}
+    for block in re.split(r"\n  - \.a", notes)[1:]:
+        value = {k: re.search(r"\.%s:\s+(\S+)" % k, block).group(1)
+                 for k in ("name", "vgpr_count", "private_segment_fixed_size")}
+        out[value["name"]] = (int(value["vgpr_count"]), int(value["private_segment_fixed_size"]))
+    return out
+
+
+def test_fourteen_samples_per_lane_keep_three_workgroups(tmp_path):
+    """Three workgroups of eight waves share a CU with at most 80 VGPRs a wave, four with at most 64."""
+    r = registers(compiled(tmp_path / "a", store="f16", nt=700, ns=16, n_dm=12, widths=W12[:-2]))
+    assert r["nsfrb_search_c14_p1_w8"][0] <= 80
+    r = registers(compiled(tmp_path / "b", store="f16", nt=700, ns=16, n_dm=12, widths=W8))
+    assert r["nsfrb_search_c14_p1_w8"][0] <= 64
