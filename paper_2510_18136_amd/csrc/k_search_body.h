@@ -95,6 +95,16 @@ __device__ __forceinline__ void copy_arr(float (&out)[C], const float (&a)[C]) {
   for (int c = 0; c < C; ++c) out[c] = a[c];
 }
 
+// After a single read of a 16-bit sample: keeps the compiler from merging it with
+// the next into wider reads, which the LDS serves at 8 to 16 bytes per clock from
+// addresses aligned to a sample only (three BF16 cubes of 64 x 64 x 16 x 700, 32
+// trials, five widths: 1.56 ms merged, 0.75 single). Lean plans leave it to the
+// compiler, with fewer registers.
+template <typename T>
+__device__ __forceinline__ void single_read() {
+  if constexpr (sizeof(T) == 2 && !NSFRB_LEAN) asm volatile("" ::: "memory");
+}
+
 // De-dispersion: cur[c] += row_s[delay_s + C * lane + c] for c < C, sub-band by
 // sub-band. Reads are grouped ahead of the adds that use them: left to itself
 // the compiler reused one register pair for a whole row, so each pair of
@@ -116,7 +126,10 @@ struct RowPart {
   __device__ __forceinline__ void load(const T* row, int dl, int l) {
     const T* r = row + dl + C * l + C0;
 #pragma unroll
-    for (int c = 0; c < N; ++c) v[c] = to_f32(r[c]);
+    for (int c = 0; c < N; ++c) {
+      v[c] = to_f32(r[c]);
+      single_read<T>();
+    }
   }
   __device__ __forceinline__ void add(float* cur, int) const {
 #pragma unroll

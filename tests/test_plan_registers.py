@@ -58,3 +58,13 @@ def test_fourteen_samples_per_lane_keep_three_workgroups(tmp_path):
     assert r["nsfrb_search_c14_p1_w8"][0] <= 80
     r = registers(compiled(tmp_path / "b", store="f16", nt=700, ns=16, n_dm=12, widths=W8))
     assert r["nsfrb_search_c14_p1_w8"][0] <= 64
+
+
+@pytest.mark.parametrize("nt,c", [(150, 3), (400, 7), (700, 11)])
+def test_single_reads_of_16_bit_rows_are_not_merged(tmp_path, nt, c):
+    """Odd rows of BF16 samples start anywhere: wider reads from such addresses are an order slower than single ones."""
+    code = compiled(tmp_path / "a", store="bf16", nt=nt, ns=16, n_dm=12, widths=W5)
+    asm = subprocess.run([LLVM + "llvm-objdump", "-d", "--no-show-raw-insn", code], capture_output=True, text=True,
+                         check=True).stdout
+    kernel = re.search(r"<nsfrb_search_c%d_p1_w8>:\n(.*?)\n\n" % c, asm, re.S).group(1)
+    assert len(re.findall(r"\bds_read_u16", kernel)) >= c
