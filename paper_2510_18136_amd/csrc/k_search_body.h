@@ -194,6 +194,51 @@ struct RowPart<T, N, true> {
   __device__ __forceinline__ void add(float* cur, int dl) const { add_pairs<N>(cur, w, T(), dl); }
 };
 
+// The leanest plans (NSFRB_LEAN 2) add each sample as it is read, cur[c] +=
+// row[dl + C * lane + c] for c < C, FP16 rows in pairs as above, in loops over the
+// rows that stand in the kernels themselves. With the row's reads gathered first,
+// or the delay behind a function, the compiler held more of a row, or two (47
+// samples per lane, BF16, eight widths, 16 waves: 420 bytes of spill a lane
+// against 48; 65 samples, FP32, five widths: 44 against 0).
+template <int C, typename T>
+__device__ __forceinline__ void add_samples(float (&cur)[C], const T* row, int dl, int l) {
+  const T* r = row + dl + C * l;
+#pragma unroll
+  for (int c = 0; c < C; ++c) cur[c] += to_f32(r[c]);
+}
+// acc + (FP16 sample in the low / high half of w), rounded once.
+__device__ __forceinline__ float add_f16_lo(float acc, uint32_t w) {
+  float r;
+  asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(acc));
+  return r;
+}
+__device__ __forceinline__ float add_f16_hi(float acc, uint32_t w) {
+  float r;
+  asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(acc));
+  return r;
+}
+template <int C>
+__device__ __forceinline__ void add_samples(float (&cur)[C], const _Float16* row, int dl, int l) {
+  static_assert((C & 1) == 0, "FP16 rows need an even number of samples per lane");
+  const uint32_t* w = reinterpret_cast<const uint32_t*>(row) + ((dl + C * l) >> 1);
+  if (dl & 1) {
+    cur[0] = add_f16_hi(cur[0], w[0]);
+#pragma unroll
+    for (int k = 0; k < C / 2; ++k) {
+      const uint32_t v = w[k + 1];
+      cur[2 * k + 1] = add_f16_lo(cur[2 * k + 1], v);
+      if (2 * k + 2 < C) cur[2 * k + 2] = add_f16_hi(cur[2 * k + 2], v);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < C / 2; ++k) {
+      const uint32_t v = w[k];
+      cur[2 * k] = add_f16_lo(cur[2 * k], v);
+      cur[2 * k + 1] = add_f16_hi(cur[2 * k + 1], v);
+    }
+  }
+}
+
 // Nothing is scheduled across: the reads above stay ahead of the adds below.
 __device__ __forceinline__ void reads_first() { __builtin_amdgcn_sched_barrier(0); }
 
@@ -296,6 +341,11 @@ __device__ __forceinline__ int locate_first(const float (&b)[C], float M, int L)
 // by DPP, the first lane L holding it by a ballot, then the first register of
 // lane L holding it (locate_first).
 constexpr int kShortC = 3;
+// A few samples per lane: the widths' reductions are short enough to run
+// interleaved, which the compiler does with its own form (1 sample: 188 against
+// 203 us for the 75x-binned survey quarter). The leanest plans leave the order to it
+// too (their sums take fewer registers so).
+constexpr bool interleaved(int C) { return C <= kShortC || NSFRB_LEAN == 2; }
 template <int C>
 __device__ __forceinline__ void max_first(const float (&b)[C], float& M, int& T) {
   constexpr int G = (C + 2) / 3;
@@ -310,10 +360,7 @@ __device__ __forceinline__ void max_first(const float (&b)[C], float& M, int& T)
   float m = g[0];
 #pragma unroll
   for (int k = 1; k < G; k += 2) m = (k + 1 < G) ? fmaxf(m, fmaxf(g[k], g[k + 1])) : fmaxf(m, g[k]);
-  // (a few samples per lane: the widths' reductions are short enough to run
-  // interleaved, which the compiler does with its own form; 1 sample: 188
-  // against 203 us for the 75x-binned survey quarter)
-  M = C <= kShortC ? wave_max_f(m) : wave_max_uniform(m);
+  M = interleaved(C) ? wave_max_f(m) : wave_max_uniform(m);
   // some lane's maximum equals M, so the ballot is never empty
   const int L = __ffsll((long long)ballot(m == M)) - 1;
   const int cf = locate_first<C>(b, M, L);
@@ -341,7 +388,7 @@ struct Reporter {
   float norm_lane;          // lane iw: sqrt(n_sub * width[iw])
   template <int C>
   __device__ __forceinline__ void emit(int iw, float M, int T) {
-    if constexpr (C <= kShortC) {
+    if constexpr (interleaved(C)) {
       const bool mine = lane_id() == iw;
       snr_lane = mine ? M : snr_lane;
       toa_lane = mine ? T : toa_lane;
@@ -507,7 +554,13 @@ __device__ __forceinline__ void search_group(const CubeDesc& cd, int p0, ST* zl,
       }
       for (int pass = 0; pass < NSFRB_NPASS; ++pass) {
         float cur[C];
-        dedisperse<C>(cur, zbase, rs, n_sub, [&](int s) { return __builtin_amdgcn_readlane(dl_cur, s); }, l);
+        if constexpr (NSFRB_LEAN == 2) {
+#pragma unroll
+          for (int c = 0; c < C; ++c) cur[c] = 0.f;
+          for (int s = 0; s < n_sub; ++s) add_samples<C>(cur, zbase + s * rs, __builtin_amdgcn_readlane(dl_cur, s), l);
+        } else {
+          dedisperse<C>(cur, zbase, rs, n_sub, [&](int s) { return __builtin_amdgcn_readlane(dl_cur, s); }, l);
+        }
         nsfrb_chain<C>(pass, cur, rep);
       }
       rep.flush();
@@ -711,11 +764,17 @@ __device__ __forceinline__ void search_pixel_dms(const CubeDesc& cd, const int* 
     }
     for (int pass = 0; pass < NSFRB_NPASS; ++pass) {
       float cur[C];
-      // (PAR: rows placed at their parity offset, see stage_rows_par)
-      dedisperse<C>(cur, zl, rs, n_sub, [&](int s) {
-        if constexpr (split_rows(C)) return __builtin_amdgcn_readlane(dlv, s);
-        else return ld_const(dd + s) + (PAR ? row_offset(par, s, n_t) : 0);
-      }, l);
+      if constexpr (NSFRB_LEAN == 2) {           // (PAR: rows placed at their parity offset, see stage_rows_par)
+#pragma unroll
+        for (int c = 0; c < C; ++c) cur[c] = 0.f;
+        for (int s = 0; s < n_sub; ++s)
+          add_samples<C>(cur, zl + s * rs, ld_const(dd + s) + (PAR ? row_offset(par, s, n_t) : 0), l);
+      } else {
+        dedisperse<C>(cur, zl, rs, n_sub, [&](int s) {
+          if constexpr (split_rows(C)) return __builtin_amdgcn_readlane(dlv, s);
+          else return ld_const(dd + s) + (PAR ? row_offset(par, s, n_t) : 0);
+        }, l);
+      }
       if (pass == NSFRB_NPASS - 1 && rd == n_rounds - 1) release();
       // a wave in its boxcar chain issues ahead of waves reading rows (the
       // row readers mostly wait on the LDS; raising the chain measured 8%

@@ -236,7 +236,7 @@ static bool rows_fit(int n_sub, int lanes, int dmax_search, int store) {
 // single reads are 16 bits wide, up to 25%). The longer rows must fit in LDS
 // (with the 16-byte row pitch of the batch and persistent kernels). A lean plan
 // reads singly.
-static int plan_samples_per_lane(int n_time, int store, int n_sub, int dmax_search, bool lean) {
+static int plan_samples_per_lane(int n_time, int store, int n_sub, int dmax_search, int lean) {
   const int lc = length_class(n_time, store);
   if (store == NSFRB_F16 || lean) return lc;
   const int c = samples_per_lane(n_time, true);
@@ -418,10 +418,10 @@ struct BatchKernel {
 // `batch`; lanes: samples per lane of each length class.
 static std::string gen_source(int store, int nw, int npass, const std::string& chain,
                               const std::vector<KernelClass>& single, const std::vector<BatchKernel>& batch,
-                              const std::vector<PersistentKernel>& persistent, const std::map<int, int>& lanes, bool lean) {
+                              const std::vector<PersistentKernel>& persistent, const std::map<int, int>& lanes, int lean) {
   std::ostringstream o;
   o << "#define NSFRB_RTC_PROLOGUE 1\n#include \"device_common.h\"\n";
-  o << "#define NSFRB_LEAN " << (lean ? 1 : 0) << "\n";
+  o << "#define NSFRB_LEAN " << lean << "\n";
   o << "#define NSFRB_NPASS " << npass << "\n";
   o << "typedef " << store_type_name(store) << " ST;\n";
   o << "#define NSFRB_NW " << nw << "\n";
@@ -614,7 +614,10 @@ extern "C" int nsfrb_debug_plan_source(const nsfrb_search_config* cfg, char* out
   compute_delays(*cfg, dl);
   const int dmax_search = max_delay_searchable(dl, cfg->n_dm, cfg->n_sub, cfg->n_time, nullptr);
   const int C = length_class(cfg->n_time, cfg->store_dtype);
-  const int lanes = plan_samples_per_lane(cfg->n_time, cfg->store_dtype, cfg->n_sub, dmax_search, false);
+  // NSFRB_DEBUG_LEAN=1 or 2 emits the lean or the leanest plan
+  const char* le = std::getenv("NSFRB_DEBUG_LEAN");
+  const int lean = le ? std::max(0, std::min(2, std::atoi(le))) : 0;
+  const int lanes = plan_samples_per_lane(cfg->n_time, cfg->store_dtype, cfg->n_sub, dmax_search, lean);
   const int rs = row_len(lanes, dmax_search, cfg->store_dtype);
   std::vector<KernelClass> ks = plan_candidates(C, cfg->n_dm, cfg->n_sub, rs, cfg->store_dtype);
   if (ks.empty()) {
@@ -636,7 +639,7 @@ extern "C" int nsfrb_debug_plan_source(const nsfrb_search_config* cfg, char* out
     bks.push_back({C, pp.NW, pp.n_buf, 1});
     bks.push_back({C, pp.NW, 1, 2});
   }
-  const std::string src = gen_source(cfg->store_dtype, cfg->n_width, npass, chain, ks, bks, pks, {{C, lanes}}, false);
+  const std::string src = gen_source(cfg->store_dtype, cfg->n_width, npass, chain, ks, bks, pks, {{C, lanes}}, lean);
   if (out && cap > 0) std::snprintf(out, (size_t)cap, "%s", src.c_str());
   if (compile) {
     std::vector<char> code;
@@ -727,7 +730,7 @@ static void release(nsfrb_search* h) {
 static nsfrb_status autotune(nsfrb_search* h, const std::vector<KernelClass>& ks);
 
 // Length class, samples per lane, LDS row length and per-DM shapes of the handle's plan.
-static void plan_rows(nsfrb_search* h, bool lean) {
+static void plan_rows(nsfrb_search* h, int lean) {
   const nsfrb_search_config& c = h->cfg;
   h->C = length_class(c.n_time, c.store_dtype);
   h->lanes = plan_samples_per_lane(c.n_time, c.store_dtype, c.n_sub, h->dmax_search, lean);
@@ -735,11 +738,23 @@ static void plan_rows(nsfrb_search* h, bool lean) {
   h->cands = plan_candidates(h->C, c.n_dm, c.n_sub, h->rs, c.store_dtype);
 }
 
-// First plan to compile: 0 is the tuned one, later ones are lean with ever
-// fewer accumulators. Above 36 samples per lane a list of more than 16 widths
-// is not tried tuned: such plans spill and take a minute to compile (4096
-// samples with 32 widths: 61 s here, lean 38 s).
-static int first_attempt(int C, int n_width) { return C > 36 && n_width > 16 ? 1 : 0; }
+// Plans in the order they are compiled until one fits: the tuned one, then lean
+// ones with ever fewer accumulators per pass, each in both its forms (1: whole
+// rows at a time; 2: the leanest, a sample at a time). 16-bit rows are faster the
+// first way (FP16, 2048 samples, 13 widths, 32 trials: 3.08 against 3.81 ms), FP32
+// rows the second (4096 samples, five widths: 1.51 against 1.60). Above 36 samples
+// per lane a list of more than 16 widths is not tried tuned: such plans spill and
+// take a minute to compile (4096 samples with 32 widths: 61 s here, lean 38 s).
+struct PlanAttempt {
+  int lean, max_acc;
+};
+static std::vector<PlanAttempt> plan_attempts(int C, int n_width, int store) {
+  std::vector<PlanAttempt> out;
+  if (!(C > 36 && n_width > 16)) out.push_back({0, kMaxAccumulators});
+  for (int acc = kMaxAccumulators; acc >= 1; --acc)
+    for (int k : {0, 1}) out.push_back({(k == 0) == (store == DT_F32) ? 2 : 1, acc});
+  return out;
+}
 
 // Compiles the handle's kernels (dropping shapes that would spill), sizes the
 // persistent grids and runs the autotuner.
@@ -758,9 +773,9 @@ static nsfrb_status plan_kernels(nsfrb_search* h) {
   // NSFRB_PERSISTENT: "0" per-DM kernel only; "NW" only the persistent kernel of NW waves (studies)
   const char* pers_env = std::getenv("NSFRB_PERSISTENT");
   const int pers_only = pers_env ? std::atoi(pers_env) : -1;
-  for (int attempt = first_attempt(h->C, cfg->n_width); attempt <= kMaxAccumulators && usable.empty(); ++attempt) {
-    const bool lean = attempt > 0;
-    const int max_acc = kMaxAccumulators - std::max(0, attempt - 1);
+  for (const PlanAttempt& at : plan_attempts(h->C, cfg->n_width, cfg->store_dtype)) {
+    if (!usable.empty()) break;
+    const int lean = at.lean, max_acc = at.max_acc;
     plan_rows(h, lean);
     std::string chain;
     int npass = 1;
@@ -836,7 +851,7 @@ static nsfrb_status search_create(const nsfrb_search_config* cfg, bool plan_now,
   h->device = cfg->device;
   compute_delays(h->cfg, h->delays);
   h->dmax_search = max_delay_searchable(h->delays, cfg->n_dm, cfg->n_sub, cfg->n_time, &h->dmaxv);
-  plan_rows(h.get(), false);
+  plan_rows(h.get(), 0);
   if (h->cands.empty())
     return fail(NSFRB_ERR_UNSUPPORTED, "n_sub x (padded n_time + max delay) does not fit in LDS for this store dtype");
   const char* force = std::getenv("NSFRB_FORCE_ALLOC_FAIL");
@@ -1353,7 +1368,7 @@ static int batch_pixels_per_item(int C, int nw, int env, size_t tile) {
 }
 
 // Kernel classes, work items and descriptors of a batch's cubes.
-static nsfrb_status batch_classes(nsfrb_batch* b, bool lean) {
+static nsfrb_status batch_classes(nsfrb_batch* b, int lean) {
   // kernel classes: cubes of the same length class; 16 waves when there
   // are at least 16 DM trials (the trials are shared by all cubes), else 8
   const nsfrb_search_config& c0 = b->cubes[0]->cfg;
@@ -1461,9 +1476,9 @@ extern "C" nsfrb_status nsfrb_batch_create(const nsfrb_search_config* cfgs, int3
   bool fits = false;
   int c_max = 0;
   for (const nsfrb_search* h : b->cubes) c_max = std::max(c_max, h->C);
-  for (int attempt = first_attempt(c_max, b->nw); attempt <= kMaxAccumulators && !fits; ++attempt) {
-    const bool lean = attempt > 0;
-    nsfrb_status st = batch_classes(b.get(), lean);
+  for (const PlanAttempt& at : plan_attempts(c_max, b->nw, b->store)) {
+    if (fits) break;
+    nsfrb_status st = batch_classes(b.get(), at.lean);
     if (st != NSFRB_OK) return st;
     std::vector<BatchKernel> ks;
     std::map<int, int> lanes;
@@ -1473,9 +1488,9 @@ extern "C" nsfrb_status nsfrb_batch_create(const nsfrb_search_config* cfgs, int3
     }
     std::string chain;
     int npass = 1;
-    st = gen_chain(b->cubes[0]->widths, chain, &npass, kMaxAccumulators - std::max(0, attempt - 1));
+    st = gen_chain(b->cubes[0]->widths, chain, &npass, at.max_acc);
     if (st != NSFRB_OK) return st;
-    st = load_module(b->device, gen_source(b->store, b->nw, npass, chain, {}, ks, {}, lanes, lean), &b->mod);
+    st = load_module(b->device, gen_source(b->store, b->nw, npass, chain, {}, ks, {}, lanes, at.lean), &b->mod);
     if (st != NSFRB_OK) return st;
     fits = true;
     for (size_t c = 0; c < b->classes.size(); ++c) {

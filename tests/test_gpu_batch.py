@@ -340,3 +340,25 @@ def test_batch_graph_after_plain_run_with_other_cubes():
         b.run(pa, stream.cuda_stream)
         same(results(b, len(cfgs)), ref_a)
     assert any(not np.array_equal(x[0], y[0]) for x, y in zip(ref_a, ref_b))
+
+
+@pytest.mark.parametrize("store,nt,widths", [("bf16", 2400, [1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 100]),
+                                             ("bf16", 3000, [1, 2, 4, 8, 16, 32, 64, 100])])
+def test_batch_of_long_series_with_many_trials_is_accepted(store, nt, widths):
+    """16-wave batch kernels at the edge of their registers: created, and bitwise equal to plain launches."""
+    stream = torch.cuda.current_stream().cuda_stream
+    cfgs, cubes = [], []
+    for k, (nx, ny) in enumerate([(7, 5), (4, 4)]):
+        c = nsfrb.SearchConfig(nx, ny, nt, np.linspace(1.311, 1.499, 16), np.linspace(0, 4000, 32), widths, in_dtype=store,
+                               store_dtype=store, norm="none", layout="pst", snr_threshold=5.0, max_candidates=16)
+        x = torch.empty(nx * ny * 16 * nt, dtype=torch.bfloat16, device="cuda")
+        nsfrb.generate_noise(x.data_ptr(), store, "pst", nx * ny, 16, nt, 40 + k, stream=stream)
+        cfgs.append(c)
+        cubes.append(x)
+    ptrs = [x.data_ptr() for x in cubes]
+    print(f"[gpu] batch of {nt} samples, {len(widths)} widths, 32 trials", flush=True)
+    with nsfrb.Batch(cfgs) as b:
+        b.run_separate(ptrs, stream)
+        ref = results(b, len(cfgs))
+        b.run(ptrs, stream)
+        same(results(b, len(cfgs)), ref)

@@ -68,3 +68,11 @@ def test_single_reads_of_16_bit_rows_are_not_merged(tmp_path, nt, c):
                          check=True).stdout
     kernel = re.search(r"<nsfrb_search_c%d_p1_w8>:\n(.*?)\n\n" % c, asm, re.S).group(1)
     assert len(re.findall(r"\bds_read_u16", kernel)) >= c
+
+
+@pytest.mark.parametrize("store,nt,ns,widths,max_acc", [("bf16", 2400, 16, W13, 1), ("bf16", 3000, 16, W8, 3),
+                                                        ("f32", 2048, 16, W13, 3), ("f32", 4096, 8, W5, 3)])
+def test_leanest_plan_spills_least(tmp_path, store, nt, ns, widths, max_acc):
+    """Batch kernels of 16 waves, 128 VGPRs: at most 64 bytes of spill, or the batch is refused."""
+    r = registers(compiled(tmp_path / "a", lean=2, max_acc=max_acc, store=store, nt=nt, ns=ns, n_dm=32, widths=widths))
+    assert r["nsfrb_batch_kernel_0"][1] <= 64
