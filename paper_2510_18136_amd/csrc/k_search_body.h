@@ -242,47 +242,52 @@ __device__ __forceinline__ void add_samples(float (&cur)[C], const _Float16* row
 // Nothing is scheduled across: the reads above stay ahead of the adds below.
 __device__ __forceinline__ void reads_first() { __builtin_amdgcn_sched_barrier(0); }
 
-// The de-dispersed series of one trial in cur. delay(s): sub-band s's delay, a
-// uniform value. Series of kSplitC samples per lane or more are read in
-// two half rows, the other half in flight while one is added. Shorter ones run
-// with enough waves to hide the read latency, and lose more by the registers
-// (waves) the second half costs (7 samples per lane: 517 against 582 us for a
-// 5x-binned survey quarter), as do lean plans (NSFRB_LEAN: the tuned one would
-// spill); they leave the order of reads and adds to the compiler.
+// De-dispersion by row reads that are grouped ahead of their adds: series of
+// kSplitC samples per lane or more are read in two half rows, the other half in
+// flight while one is added (sub-band s's delay in lane s of dlv; with the delay
+// behind a function this loop too held a second row: 35 samples, FP32, five
+// widths, 16 waves: 52 bytes of spill against 0). Shorter ones run with enough
+// waves to hide the read latency, and lose more by the registers (waves) the
+// second half costs (7 samples per lane: 517 against 582 us for a 5x-binned
+// survey quarter), as do lean plans (NSFRB_LEAN: the tuned one would spill); they
+// leave the order of reads and adds to the compiler. delay(s): sub-band s's delay,
+// a uniform value.
 constexpr int kSplitC = 20;
 constexpr bool split_rows(int C) { return C >= kSplitC && !NSFRB_LEAN; }
 template <int C, typename T, class Delay>
 __device__ __forceinline__ void dedisperse(float (&cur)[C], const T* rows, int rs, int n_sub, const Delay& delay, int l) {
 #pragma unroll
   for (int c = 0; c < C; ++c) cur[c] = 0.f;
+  for (int s = 0; s < n_sub; ++s) {
+    const int dl = delay(s);
+    RowPart<T, C, (C & 1) == 0> a;
+    a.template load<C, 0>(rows + s * rs, dl, l);
+    a.add(cur, dl);
+  }
+}
+template <int C, typename T>
+__device__ __forceinline__ void dedisperse_split(float (&cur)[C], const T* rows, int rs, int n_sub, int dlv, int l) {
+#pragma unroll
+  for (int c = 0; c < C; ++c) cur[c] = 0.f;
   constexpr bool paired = (C & 1) == 0;
-  if constexpr (!split_rows(C)) {
-    for (int s = 0; s < n_sub; ++s) {
-      const int dl = delay(s);
-      RowPart<T, C, paired> a;
-      a.template load<C, 0>(rows + s * rs, dl, l);
-      a.add(cur, dl);
-    }
-  } else {
-    constexpr int H = (C / 2 + 1) & ~1;                  // even, about half a row
-    RowPart<T, H, paired> a;
-    RowPart<T, C - H, paired> b;
-    int dl = delay(0);
-    a.template load<C, 0>(rows, dl, l);
-    for (int s = 0; s < n_sub; ++s) {
-      b.template load<C, H>(rows + s * rs, dl, l);
-      reads_first();
-      a.add(cur, dl, b);
-      // (the last row's first half is read once more: a branch around the reads
-      // would make the compiler copy the registers)
-      const int sn = s + 1 < n_sub ? s + 1 : s;
-      const int dn = delay(sn);
-      reads_first();
-      a.template load<C, 0>(rows + sn * rs, dn, l);
-      reads_first();
-      b.add(cur + H, dl);
-      dl = dn;
-    }
+  constexpr int H = (C / 2 + 1) & ~1;                  // even, about half a row
+  RowPart<T, H, paired> a;
+  RowPart<T, C - H, paired> b;
+  int dl = __builtin_amdgcn_readlane(dlv, 0);
+  a.template load<C, 0>(rows, dl, l);
+  for (int s = 0; s < n_sub; ++s) {
+    b.template load<C, H>(rows + s * rs, dl, l);
+    reads_first();
+    a.add(cur, dl, b);
+    // (the last row's first half is read once more: a branch around the reads
+    // would make the compiler copy the registers)
+    const int sn = s + 1 < n_sub ? s + 1 : s;
+    const int dn = __builtin_amdgcn_readlane(dlv, sn);
+    reads_first();
+    a.template load<C, 0>(rows + sn * rs, dn, l);
+    reads_first();
+    b.add(cur + H, dl);
+    dl = dn;
   }
 }
 
@@ -554,7 +559,9 @@ __device__ __forceinline__ void search_group(const CubeDesc& cd, int p0, ST* zl,
       }
       for (int pass = 0; pass < NSFRB_NPASS; ++pass) {
         float cur[C];
-        if constexpr (NSFRB_LEAN == 2) {
+        if constexpr (split_rows(C)) {
+          dedisperse_split<C>(cur, zbase, rs, n_sub, dl_cur, l);
+        } else if constexpr (NSFRB_LEAN == 2) {
 #pragma unroll
           for (int c = 0; c < C; ++c) cur[c] = 0.f;
           for (int s = 0; s < n_sub; ++s) add_samples<C>(cur, zbase + s * rs, __builtin_amdgcn_readlane(dl_cur, s), l);
@@ -764,16 +771,15 @@ __device__ __forceinline__ void search_pixel_dms(const CubeDesc& cd, const int* 
     }
     for (int pass = 0; pass < NSFRB_NPASS; ++pass) {
       float cur[C];
-      if constexpr (NSFRB_LEAN == 2) {           // (PAR: rows placed at their parity offset, see stage_rows_par)
+      if constexpr (split_rows(C)) {
+        dedisperse_split<C>(cur, zl, rs, n_sub, dlv, l);
+      } else if constexpr (NSFRB_LEAN == 2) {    // (PAR: rows placed at their parity offset, see stage_rows_par)
 #pragma unroll
         for (int c = 0; c < C; ++c) cur[c] = 0.f;
         for (int s = 0; s < n_sub; ++s)
           add_samples<C>(cur, zl + s * rs, ld_const(dd + s) + (PAR ? row_offset(par, s, n_t) : 0), l);
       } else {
-        dedisperse<C>(cur, zl, rs, n_sub, [&](int s) {
-          if constexpr (split_rows(C)) return __builtin_amdgcn_readlane(dlv, s);
-          else return ld_const(dd + s) + (PAR ? row_offset(par, s, n_t) : 0);
-        }, l);
+        dedisperse<C>(cur, zl, rs, n_sub, [&](int s) { return ld_const(dd + s) + (PAR ? row_offset(par, s, n_t) : 0); }, l);
       }
       if (pass == NSFRB_NPASS - 1 && rd == n_rounds - 1) release();
       // a wave in its boxcar chain issues ahead of waves reading rows (the

@@ -76,3 +76,8 @@ def test_leanest_plan_spills_least(tmp_path, store, nt, ns, widths, max_acc):
     """Batch kernels of 16 waves, 128 VGPRs: at most 64 bytes of spill, or the batch is refused."""
     r = registers(compiled(tmp_path / "a", lean=2, max_acc=max_acc, store=store, nt=nt, ns=ns, n_dm=32, widths=widths))
     assert r["nsfrb_batch_kernel_0"][1] <= 64
+
+
+def test_rows_read_in_halves_hold_one_row(tmp_path):
+    r = registers(compiled(tmp_path / "a", store="f32", nt=2176, ns=16, n_dm=32, widths=W5))
+    assert r["nsfrb_batch_kernel_0"][1] == 0 and r["nsfrb_persistent_c35_w16_b1"][1] == 0
