@@ -156,6 +156,7 @@ struct KernelClass {
   int C;     // length class (see length_class)
   int PIX;   // pixels per workgroup
   int NW;    // waves per workgroup (8 or 16)
+  bool capped = false;   // held to 128 VGPRs (see capped_form)
 };
 std::string single_kernel_name(const KernelClass& k);
 // DM-trial grid from a smearing tolerance (see nsfrb.h): with A = 4.15 ms *
@@ -412,7 +413,11 @@ struct PersistentKernel {
 // A persistent batch kernel: samples per lane, waves, LDS buffers, pixels per item.
 struct BatchKernel {
   int C, NW, n_buf, pix;
+  bool capped = false;   // beside it, its form held to 128 VGPRs (see capped_form)
 };
+static std::string batch_kernel_name(size_t i, bool capped) {
+  return "nsfrb_batch_kernel_" + std::to_string(i) + (capped ? "_v128" : "");
+}
 // Translation unit with the per-DM kernels of `single` (C, PIX, NW), the
 // persistent single-cube kernels, and one persistent batch kernel per entry of
 // `batch`; lanes: samples per lane of each length class.
@@ -441,34 +446,30 @@ static std::string gen_source(int store, int nw, int npass, const std::string& c
   }
   for (int n : parts) o << gen_add_pairs(n, store);
   o << chain;
-  // Two 8-wave workgroups share a CU where their rows leave room: at most 128
-  // VGPRs. Width lists with accumulators need a few more at 30 to 34 samples per
-  // lane (FP16 survey: 130), which a few bytes of spill make up for; other
-  // series stay below by themselves or would spill too much.
-  const bool acc = chain.find("copy_arr") != std::string::npos;
-  auto bounds = [&](int C, int NW) {
-    const bool cap = NW == 8 && acc && lanes.at(C) >= 30 && lanes.at(C) <= 34 && !lean;
-    return "__launch_bounds__(" + std::to_string(64 * NW) + ")" + (cap ? " __attribute__((amdgpu_waves_per_eu(4)))" : "");
-  };
+  static const char kCap[] = " __attribute__((amdgpu_waves_per_eu(4)))";
+  auto bounds = [](int NW) { return "__launch_bounds__(" + std::to_string(64 * NW) + ")"; };
   for (const auto& k : single)
-    o << "extern \"C\" __global__ " << bounds(k.C, k.NW) << " void " << single_kernel_name(k)
-      << "(nsfrb::CubeDesc cd) { search_cube<" << k.C << ", " << k.PIX << ", " << k.NW << ">(cd); }\n";
+    o << "extern \"C\" __global__ " << bounds(k.NW) << (k.capped ? kCap : "") << " void "
+      << single_kernel_name(k) << "(nsfrb::CubeDesc cd) { search_cube<" << k.C << ", " << k.PIX << ", " << k.NW
+      << ">(cd); }\n";
   for (const auto& k : persistent)
-    o << "extern \"C\" __global__ " << bounds(k.C, k.NW) << " void nsfrb_persistent_c" << k.C << "_w"
+    o << "extern \"C\" __global__ " << bounds(k.NW) << " void nsfrb_persistent_c" << k.C << "_w"
       << k.NW << "_b" << k.n_buf
       << "(nsfrb::CubeDesc cd, const int* __restrict__ delays, const int* __restrict__ dmax) { "
          "nsfrb::search_persistent<" << k.C << ", " << k.NW << ", " << k.n_buf << ">(cd, delays, dmax); }\n";
   // one persistent kernel per class of the batch
   for (size_t i = 0; i < batch.size(); ++i)
-    o << "extern \"C\" __global__ " << bounds(batch[i].C, batch[i].NW) << " void nsfrb_batch_kernel_" << i
-      << "(const nsfrb::CubeDesc* __restrict__ descs, int n_cubes, long long n_items, int buf_stride) {\n"
-         "  nsfrb::search_batch_persistent<" << batch[i].C << ", " << batch[i].NW << ", " << batch[i].n_buf << ", "
-      << batch[i].pix << ">(descs, n_cubes, n_items, buf_stride);\n}\n";
+    for (int capped = 0; capped <= (batch[i].capped ? 1 : 0); ++capped)
+      o << "extern \"C\" __global__ " << bounds(batch[i].NW) << (capped ? kCap : "") << " void " << batch_kernel_name(i, capped)
+        << "(const nsfrb::CubeDesc* __restrict__ descs, int n_cubes, long long n_items, int buf_stride) {\n"
+           "  nsfrb::search_batch_persistent<" << batch[i].C << ", " << batch[i].NW << ", " << batch[i].n_buf << ", "
+        << batch[i].pix << ">(descs, n_cubes, n_items, buf_stride);\n}\n";
   return o.str();
 }
 
 std::string single_kernel_name(const KernelClass& k) {
-  return "nsfrb_search_c" + std::to_string(k.C) + "_p" + std::to_string(k.PIX) + "_w" + std::to_string(k.NW);
+  return "nsfrb_search_c" + std::to_string(k.C) + "_p" + std::to_string(k.PIX) + "_w" + std::to_string(k.NW) +
+         (k.capped ? "_v128" : "");
 }
 
 // Compiled modules, shared by every handle on a device.
@@ -557,6 +558,28 @@ static std::vector<KernelClass> plan_candidates(int C, int n_dm, int n_sub, int 
   return out;
 }
 
+// Two 8-wave workgroups share a CU where their LDS (lds: bytes of one) leaves room
+// and a wave takes at most 128 VGPRs. Width lists with accumulators need a few
+// more from 30 samples per lane on (16-bit survey: 130), which a few bytes of
+// spill make up for: beside such a kernel stands its form held to 128. Shorter
+// series stay below by themselves; from 39 samples on three arrays of them leave
+// no room in 128. FP16, 12 DM trials, three cubes of 64 x 64 x 16, the form held
+// to 128 against the free one: 2048 samples, 12 widths to 1200: 0.85 against
+// 1.21 ms; 1800 samples, 13 widths: 0.77 against 1.02.
+static bool capped_form(const std::string& chain, int NW, int lanes, size_t lds) {
+  return NW == 8 && chain.find("copy_arr") != std::string::npos && lanes >= 30 && lanes <= 38 && 2 * (lds + 1024) <= 160 * 1024;
+}
+// The shapes with such forms added: the autotuner chooses. (A persistent kernel of
+// one cube gets none: it is used only without any spill, whose reload would wait
+// for the row requests in flight.)
+static std::vector<KernelClass> with_capped_forms(std::vector<KernelClass> ks, const std::string& chain, int lanes, int n_sub,
+                                                  int rs, int store) {
+  for (size_t i = 0, n = ks.size(); i < n; ++i)
+    if (capped_form(chain, ks[i].NW, lanes, lds_bytes_for(ks[i].PIX, n_sub, rs, store)))
+      ks.push_back({ks[i].C, ks[i].PIX, ks[i].NW, true});
+  return ks;
+}
+
 // ------------------------------------------------ persistent kernel plans
 // The persistent kernel keeps one pixel per workgroup of NW waves (DM trials
 // round-robin, as the per-DM kernel) and walks its pixels (ItemWalk);
@@ -639,6 +662,9 @@ extern "C" int nsfrb_debug_plan_source(const nsfrb_search_config* cfg, char* out
     bks.push_back({C, pp.NW, pp.n_buf, 1});
     bks.push_back({C, pp.NW, 1, 2});
   }
+  ks = with_capped_forms(ks, chain, lanes, cfg->n_sub, rs, cfg->store_dtype);
+  for (BatchKernel& k : bks)
+    k.capped = capped_form(chain, k.NW, lanes, (size_t)k.n_buf * lds_bytes_for(k.pix, cfg->n_sub, (rs + 7) / 8 * 8, cfg->store_dtype));
   const std::string src = gen_source(cfg->store_dtype, cfg->n_width, npass, chain, ks, bks, pks, {{C, lanes}}, lean);
   if (out && cap > 0) std::snprintf(out, (size_t)cap, "%s", src.c_str());
   if (compile) {
@@ -655,6 +681,7 @@ struct nsfrb_search {
   std::vector<int32_t> widths, delays, dmaxv;
   int n_pix = 0, device = 0;
   int C = 0, pix = 1, nw = 8;          // chosen kernel class
+  bool capped = false;                 // its form held to 128 VGPRs
   int lanes = 0, rs = 0;               // samples per lane and LDS row length
   int dmax_search = 0;                 // largest delay of a searchable trial
   int max_acc = kMaxAccumulators;      // accumulators per pass of the boxcar plan (no register spills)
@@ -788,10 +815,11 @@ static nsfrb_status plan_kernels(nsfrb_search* h) {
         if (pers_only < 0 || pp.NW == pers_only) pps.push_back(pp);
     std::vector<PersistentKernel> pks;
     for (const PersistentPlan& pp : pps) pks.push_back({h->C, pp.NW, pp.n_buf});
-    h->source = gen_source(cfg->store_dtype, cfg->n_width, npass, chain, h->cands, {}, pks, {{h->C, h->lanes}}, lean);
+    const std::vector<KernelClass> shapes = with_capped_forms(h->cands, chain, h->lanes, cfg->n_sub, h->rs, cfg->store_dtype);
+    h->source = gen_source(cfg->store_dtype, cfg->n_width, npass, chain, shapes, {}, pks, {{h->C, h->lanes}}, lean);
     st = load_module(h->device, h->source, &h->mod);
     if (st != NSFRB_OK) return st;
-    for (const KernelClass& k : h->cands) {
+    for (const KernelClass& k : shapes) {
       hipFunction_t fn = nullptr;
       HIP_TRY(hipModuleGetFunction(&fn, h->mod, single_kernel_name(k).c_str()));
       int scratch = 0;
@@ -996,7 +1024,9 @@ struct TuneKey {
   }
 };
 struct TuneChoice {
-  int pix, nw, pers;      // pers: index of the persistent candidate used, -1 for the per-DM kernel
+  int pix, nw;
+  bool capped;
+  int pers;               // index of the persistent candidate used, -1 for the per-DM kernel
 };
 static std::mutex g_tune_mu;
 static std::map<TuneKey, TuneChoice> g_tune_cache;
@@ -1006,7 +1036,7 @@ static nsfrb_status autotune(nsfrb_search* h, const std::vector<KernelClass>& ks
   std::vector<hipFunction_t> fns(ks.size());
   for (size_t i = 0; i < ks.size(); ++i)
     HIP_TRY(hipModuleGetFunction(&fns[i], h->mod, single_kernel_name(ks[i]).c_str()));
-  auto choose = [&](size_t i) { h->pix = ks[i].PIX; h->nw = ks[i].NW; h->search_fn = fns[i]; };
+  auto choose = [&](size_t i) { h->pix = ks[i].PIX; h->nw = ks[i].NW; h->capped = ks[i].capped; h->search_fn = fns[i]; };
   auto choose_pers = [&](int i) { h->pers = (i >= 0 && i < (int)h->pers_plans.size()) ? i : -1; };
   choose(0);
   h->pers = -1;
@@ -1031,7 +1061,7 @@ static nsfrb_status autotune(nsfrb_search* h, const std::vector<KernelClass>& ks
     auto it = g_tune_cache.find(key);
     if (it != g_tune_cache.end()) {
       for (size_t i = 0; i < ks.size(); ++i)
-        if (ks[i].PIX == it->second.pix && ks[i].NW == it->second.nw) choose(i);
+        if (ks[i].PIX == it->second.pix && ks[i].NW == it->second.nw && ks[i].capped == it->second.capped) choose(i);
       choose_pers(it->second.pers);
       return NSFRB_OK;
     }
@@ -1082,7 +1112,7 @@ static nsfrb_status autotune(nsfrb_search* h, const std::vector<KernelClass>& ks
   hipEventDestroy(e0);
   hipEventDestroy(e1);
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tune_cache[key] = {h->pix, h->nw, h->pers};
+  g_tune_cache[key] = {h->pix, h->nw, h->capped, h->pers};
   return NSFRB_OK;
 }
 
@@ -1469,49 +1499,55 @@ extern "C" nsfrb_status nsfrb_batch_create(const nsfrb_search_config* cfgs, int3
   }
   // one module with a persistent kernel per class; like a single cube's plan it
   // is regenerated lean, then with fewer accumulators per pass, while a class
-  // kernel would spill more than a search kernel may, and refused only after that
+  // kernel would spill more than a search kernel may, and refused only after
+  // that. Of a class's kernel and its form held to 128 VGPRs the first is taken
+  // that two workgroups of share a CU, else the first that spills too little.
   HIP_TRY(hipSetDevice(b->device));
   int n_cu = 0;
   HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, b->device));
-  bool fits = false;
   int c_max = 0;
   for (const nsfrb_search* h : b->cubes) c_max = std::max(c_max, h->C);
+  bool fits = false;
   for (const PlanAttempt& at : plan_attempts(c_max, b->nw, b->store)) {
     if (fits) break;
     nsfrb_status st = batch_classes(b.get(), at.lean);
     if (st != NSFRB_OK) return st;
-    std::vector<BatchKernel> ks;
-    std::map<int, int> lanes;
-    for (const auto& bc : b->classes) {
-      ks.push_back({bc.k.C, bc.k.NW, bc.n_buf, bc.k.PIX});
-      lanes[bc.k.C] = bc.lanes;
-    }
     std::string chain;
     int npass = 1;
     st = gen_chain(b->cubes[0]->widths, chain, &npass, at.max_acc);
     if (st != NSFRB_OK) return st;
+    std::vector<BatchKernel> ks;
+    std::map<int, int> lanes;
+    for (const auto& bc : b->classes) {
+      ks.push_back({bc.k.C, bc.k.NW, bc.n_buf, bc.k.PIX, capped_form(chain, bc.k.NW, bc.lanes, bc.lds)});
+      lanes[bc.k.C] = bc.lanes;
+    }
     st = load_module(b->device, gen_source(b->store, b->nw, npass, chain, {}, ks, {}, lanes, at.lean), &b->mod);
     if (st != NSFRB_OK) return st;
     fits = true;
-    for (size_t c = 0; c < b->classes.size(); ++c) {
+    for (size_t c = 0; c < b->classes.size() && fits; ++c) {
       BatchClass& bc = b->classes[c];
-      HIP_TRY(hipModuleGetFunction(&bc.fn, b->mod, ("nsfrb_batch_kernel_" + std::to_string(c)).c_str()));
-      int scratch = 0;
-      HIP_TRY(hipFuncGetAttribute(&scratch, HIP_FUNC_ATTRIBUTE_LOCAL_SIZE_BYTES, bc.fn));
-      fits = fits && scratch <= scratch_allowance();
+      int best = 0;                      // workgroups per CU of the form taken
+      for (int capped = 0; capped <= (ks[c].capped && best < 2 ? 1 : 0); ++capped) {
+        hipFunction_t fn = nullptr;
+        int scratch = 0, per_cu = 0;
+        HIP_TRY(hipModuleGetFunction(&fn, b->mod, batch_kernel_name(c, capped).c_str()));
+        HIP_TRY(hipFuncGetAttribute(&scratch, HIP_FUNC_ATTRIBUTE_LOCAL_SIZE_BYTES, fn));
+        if (scratch > scratch_allowance()) continue;
+        HIP_TRY(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64 * bc.k.NW, bc.lds));
+        per_cu = std::max(1, per_cu);
+        if (per_cu <= best) continue;
+        best = per_cu;
+        bc.fn = fn;
+        // a persistent grid of as many workgroups as this kernel keeps resident
+        bc.grid = (unsigned)std::max(1LL, std::min((long long)n_cu * per_cu, bc.n_items));
+      }
+      fits = best > 0;
     }
   }
   if (!fits)
     return fail(NSFRB_ERR_UNSUPPORTED, "a class's persistent kernel would spill more registers than a search kernel "
                                        "may at every accumulator count");
-  for (size_t c = 0; c < b->classes.size(); ++c) {
-    BatchClass& bc = b->classes[c];
-    // a persistent grid of as many workgroups as this class's kernel keeps resident
-    int per_cu = 0;
-    HIP_TRY(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, bc.fn, 64 * bc.k.NW, bc.lds));
-    const long long g = (long long)n_cu * std::max(1, per_cu);
-    bc.grid = (unsigned)std::max(1LL, std::min(g, bc.n_items));
-  }
   HIP_TRY(dalloc(&b->d_descs, b->descs.size()));
   std::vector<CandDesc> cands;
   bool short_lists = true;

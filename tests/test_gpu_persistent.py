@@ -77,3 +77,14 @@ def test_every_kernel_form_gives_the_same_results(monkeypatch, n_dm, nx, ny, nt,
         assert g["cands"] == ref["cands"] and g["n_total"] == ref["n_total"], mode
     if store == "f32" and nt <= 512:
         compare(ref, oracle_run(cube, cfg), cfg)
+
+
+def test_plan_with_fewer_trials_than_waves_keeps_its_persistent_kernel(monkeypatch):
+    """12 DM trials, a width that needs an accumulator: the 8-wave persistent kernel, the only one, has no spill."""
+    cfg = nsfrb.SearchConfig(9, 7, 2048, FREQS, np.linspace(0, 4000, 12), [1, 2, 4, 8, 16, 32, 64, 128, 256, 512, 1024, 1200],
+                             store_dtype="f16", snr_threshold=6.0)
+    cube = pulsed_cube(2048, 63, 5)
+    out = forms(monkeypatch, cfg, cube)
+    assert set(out) == {"0", "8"}
+    for k in ("snr", "toa"):
+        np.testing.assert_array_equal(out["8"][k], out["0"][k])

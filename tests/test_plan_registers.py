@@ -81,3 +81,18 @@ def test_leanest_plan_spills_least(tmp_path, store, nt, ns, widths, max_acc):
 def test_rows_read_in_halves_hold_one_row(tmp_path):
     r = registers(compiled(tmp_path / "a", store="f32", nt=2176, ns=16, n_dm=32, widths=W5))
     assert r["nsfrb_batch_kernel_0"][1] == 0 and r["nsfrb_persistent_c35_w16_b1"][1] == 0
+
+
+@pytest.mark.parametrize("store,widths", [("f16", W12), ("bf16", W12), ("f16", W13)])
+def test_forms_held_to_128_registers_stand_beside_the_free_ones(tmp_path, store, widths):
+    """The persistent kernel keeps its registers (a spill would drop it); two workgroups fit beside that."""
+    r = registers(compiled(tmp_path / "a", store=store, nt=2048, ns=16, n_dm=12, widths=widths))
+    c = 34 if store == "f16" else 33
+    assert r["nsfrb_persistent_c%d_w8_b1" % c][1] == 0
+    for name in ("nsfrb_search_c%d_p1_w8" % c, "nsfrb_batch_kernel_0"):
+        assert r[name][1] == 0 and r[name + "_v128"][0] <= 128
+
+
+def test_no_held_form_where_one_workgroup_fills_the_lds(tmp_path):
+    r = registers(compiled(tmp_path / "a", store="f32", nt=2048, ns=16, n_dm=12, widths=W12))
+    assert r["nsfrb_batch_kernel_0"][1] == 0 and not any(k.endswith("_v128") for k in r)
