@@ -75,11 +75,18 @@ __device__ __forceinline__ uint32_t kth_largest(const uint32_t (&key)[N], int K,
   return T;
 }
 
+// A workgroup's LDS, declared by the kernels: the batch kernel holds every PER's
+// code, and an array of each's own would be four times this.
+struct TopShared {
+  unsigned long long s[kTopMerge];
+  int sh[2 * kTopThreads / kWave], fill, last;
+};
+
 // Pixels PER * kTopThreads of one cube by one workgroup.
 template <int PER>
-__device__ __forceinline__ void cand_top(const CandDesc& d, int blk) {
-  __shared__ unsigned long long s[kTopMerge];
-  __shared__ int sh[2 * kTopThreads / kWave], fill, last;
+__device__ __forceinline__ void cand_top(const CandDesc& d, int blk, TopShared& lds) {
+  unsigned long long* s = lds.s;
+  int *sh = lds.sh, &fill = lds.fill, &last = lds.last;
   if (blk >= d.blocks) return;
   const int tid = threadIdx.x, K = d.k_max;
   const int p0 = blk * PER * kTopThreads;
@@ -202,16 +209,18 @@ __device__ __forceinline__ void cand_top(const CandDesc& d, int blk) {
 
 template <int PER>
 __global__ __launch_bounds__(kTopThreads) void k_cand_top(CandDesc d) {
-  cand_top<PER>(d, blockIdx.x);
+  __shared__ TopShared lds;
+  cand_top<PER>(d, blockIdx.x, lds);
 }
 // Cube blockIdx.y of a batch.
 __global__ __launch_bounds__(kTopThreads) void k_cand_top_batch(const CandDesc* __restrict__ descs) {
+  __shared__ TopShared lds;
   const CandDesc d = descs[blockIdx.y];
   switch (d.per) {
-    case 4: cand_top<4>(d, blockIdx.x); break;
-    case 8: cand_top<8>(d, blockIdx.x); break;
-    case 16: cand_top<16>(d, blockIdx.x); break;
-    default: cand_top<kTopMaxPer>(d, blockIdx.x);
+    case 4: cand_top<4>(d, blockIdx.x, lds); break;
+    case 8: cand_top<8>(d, blockIdx.x, lds); break;
+    case 16: cand_top<16>(d, blockIdx.x, lds); break;
+    default: cand_top<kTopMaxPer>(d, blockIdx.x, lds);
   }
 }
 

@@ -43,3 +43,19 @@ def test_every_wave_waits_for_its_keys_before_the_ticket(assembly):
             between = code[store + 1:barrier]
             assert any(c.startswith("buffer_wbl2") and "sc1" in c for c in between), name
             assert any(c.startswith("s_waitcnt") and "vmcnt(0)" in c for c in between), name
+
+
+def lds_bytes(assembly):
+    """{kernel: bytes of LDS a workgroup}"""
+    out = {}
+    for block in re.split(r"\n  - \.a", assembly)[1:]:
+        out[re.search(r"\.name:\s+(\S+)", block).group(1)] = int(
+            re.search(r"\.group_segment_fixed_size:\s+(\d+)", block).group(1))
+    return out
+
+
+def test_the_batch_kernel_takes_one_workgroup_s_lds(assembly):
+    """It holds the code of four sizes; each with LDS of its own, one workgroup filled a CU."""
+    lds = {k: v for k, v in lds_bytes(assembly).items() if "k_cand_top" in k}
+    assert len(lds) == 5
+    assert max(lds.values()) == min(lds.values())
