@@ -59,3 +59,10 @@ def test_the_batch_kernel_takes_one_workgroup_s_lds(assembly):
     lds = {k: v for k, v in lds_bytes(assembly).items() if "k_cand_top" in k}
     assert len(lds) == 5
     assert max(lds.values()) == min(lds.values())
+
+
+def test_only_the_keys_kept_are_ranked(assembly):
+    """Ranking is quadratic: no more than 256 keys of 8 bytes may reach it, however many are tied."""
+    for name, size in lds_bytes(assembly).items():
+        if "k_cand_top" in name:
+            assert size <= 256 * 8 + 64, name
