@@ -9,7 +9,7 @@
 // This file is compiled at plan time. The generated prologue fixes the store
 // dtype (ST), the number of widths (NSFRB_NW), the shape classes and the samples
 // per lane C of each length class LC (lane_samples: where rows are read in
-// pairs C is even, at most three more than LC); the generated boxcar plan
+// pairs C is even, at most three more than LC or one fewer); the generated boxcar plan
 // (nsfrb_chain) follows this file. DM trials, delays,
 // n_sub and n_t stay runtime values.
 //

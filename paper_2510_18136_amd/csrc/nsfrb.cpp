@@ -1323,7 +1323,7 @@ extern "C" nsfrb_status nsfrb_search_plan_info(const nsfrb_search* h, int32_t* i
   if (!h || !info) return fail(NSFRB_ERR_INVALID_ARG, "NULL argument");
   const bool pe = h->pers >= 0;
   const PersistentPlan* pp = pe ? &h->pers_plans[(size_t)h->pers] : nullptr;
-  info[0] = h->C;
+  info[0] = h->lanes;
   info[1] = pe ? 1 : h->pix;
   info[2] = pe ? pp->rs : h->rs;
   info[3] = (int32_t)(pe ? pp->lds : h->lds_bytes);

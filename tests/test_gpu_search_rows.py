@@ -63,3 +63,12 @@ def test_paired_rows_only_where_they_fit(store, ns, c):
 def test_lean_plan():
     """A long series with many widths: the plan that spends the fewest registers."""
     check(2400, 4, "f32", list(range(1, 18)), np.linspace(0.0, 1000.0, 4), nx=2, ny=1)
+
+
+@pytest.mark.parametrize("store,nt,c", [("f32", 2048, 34), ("f32", 2176, 35), ("f16", 2048, 34), ("bf16", 2048, 34),
+                                        ("bf16", 700, 11), ("f32", 333, 6)])
+def test_plan_info_names_the_samples_per_lane_that_run(store, nt, c):
+    cfg = nsfrb.SearchConfig(3, 2, nt, np.linspace(1.311, 1.499, 5), np.linspace(0.0, 500.0, 3), [1, 2, 4], store_dtype=store)
+    with nsfrb.Search(cfg) as s:
+        info, dmax = s.plan_info(), int(s.delay_table().max())
+    assert info["samples_per_lane"] == (info["row_len"] - 1 - dmax) // 64 == c
