@@ -770,16 +770,22 @@ static void plan_rows(nsfrb_search* h, int lean) {
 // rows at a time; 2: the leanest, a sample at a time). 16-bit rows are faster the
 // first way (FP16, 2048 samples, 13 widths, 32 trials: 3.08 against 3.81 ms), FP32
 // rows the second (4096 samples, five widths: 1.51 against 1.60). Above 36 samples
-// per lane a list of more than 16 widths is not tried tuned: such plans spill and
-// take a minute to compile (4096 samples with 32 widths: 61 s here, lean 38 s).
+// per lane a list of more than 16 widths is tried in the faster lean form only:
+// such plans take a minute to compile (4096 samples with 32 widths: 61 s tuned, 38
+// lean), tuned ones spill, and both lean forms fit at the same accumulators (2400
+// and 4096 samples with 17 and 24 widths, each store type).
 struct PlanAttempt {
   int lean, max_acc;
 };
 static std::vector<PlanAttempt> plan_attempts(int C, int n_width, int store) {
   std::vector<PlanAttempt> out;
-  if (!(C > 36 && n_width > 16)) out.push_back({0, kMaxAccumulators});
-  for (int acc = kMaxAccumulators; acc >= 1; --acc)
-    for (int k : {0, 1}) out.push_back({(k == 0) == (store == DT_F32) ? 2 : 1, acc});
+  const int first = store == DT_F32 ? 2 : 1;
+  const bool heavy = C > 36 && n_width > 16;
+  if (!heavy) out.push_back({0, kMaxAccumulators});
+  for (int acc = kMaxAccumulators; acc >= 1; --acc) {
+    out.push_back({first, acc});
+    if (!heavy) out.push_back({3 - first, acc});
+  }
   return out;
 }
 
