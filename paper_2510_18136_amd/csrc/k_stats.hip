@@ -296,12 +296,12 @@ __device__ __forceinline__ void two_ranks(T c, uint64_t mask, int k, bool want_s
 // `tie` that all of them share. lo, hi: the last round's range; first, last: the
 // members' products in it.
 struct Picked {
-  float v, tie;
-  uint64_t mask;
-  int krem;
-  float lo, hi, scale;
-  uint32_t first, last;
-  bool ok, one;          // decided; by one round over all samples
+  float v = 0.0f, tie = 0.0f;
+  uint64_t mask = 0;
+  int krem = 0;
+  float lo = 0.0f, hi = 0.0f, scale = 0.0f;
+  uint32_t first = 0, last = 0;
+  bool ok = false, one = false;   // decided; by one round over all samples (not so for equal samples, which take none)
 };
 
 // Candidates of a wave: each lane writes those among its samples to slots of its
@@ -454,8 +454,6 @@ __device__ __forceinline__ Picked pick(const float (&x)[V], float c, float lo, f
   RoundRange r{c, lo, hi, 0.0f, 8388608.0f + (float)hb, 0u, 3u};
   u32x4* h4 = (u32x4*)cx.hist + l;
   Picked p;
-  p.ok = false;
-  p.mask = 0;
   p.tie = lo;
   p.krem = k;
   bool check = !full;

@@ -131,3 +131,12 @@ def test_rank_at_the_edge_of_a_crowded_bin(nt, edge):
     assert x.shape == (64, nt) and (x == x.astype(np.float32)).all()
     assert (np.median(x, axis=1) == 1.0 + 2.0 ** -24).all()
     check(x.T[:, None], 8, 8)
+
+
+@pytest.mark.parametrize("nt", [1, 64, 500, 700, 1024, 2047, 2048, 4096])
+def test_equal_samples(nt):
+    """Selection takes no histogram round for them: nothing of one may be used after it. Beside them, ordinary series."""
+    rng = np.random.default_rng(nt)
+    x = rng.standard_normal((nt, 2, 32))
+    x[:, :, ::2] = rng.choice([0.0, -0.0, 1.0, -3.7e30, 1e-42, 4096.5], (1, 2, 16))
+    check(x, 8, 4)
