@@ -293,14 +293,14 @@ __device__ __forceinline__ void two_ranks(T c, uint64_t mask, int k, bool want_s
 
 // What the histogram rounds end with: up to 64 members, one in each lane of
 // `mask` in v, among which the wanted rank is krem; or no mask and the one key
-// `tie` that all of them share. lo, hi: the last round's range; first, last: the
-// members' products in it.
+// `tie` that all of them share. t_lo and t_hi bound the members' keys: those of
+// all other samples lie outside.
 struct Picked {
-  float v = 0.0f, tie = 0.0f;
-  uint64_t mask = 0;
-  int krem = 0;
-  float lo = 0.0f, hi = 0.0f, scale = 0.0f;
-  uint32_t first = 0, last = 0;
+  float v, tie;
+  uint64_t mask;
+  int krem;
+  double t_lo, t_hi;
+  float scale = 0.0f;    // of the last round
   bool ok = false, one = false;   // decided; by one round over all samples (not so for equal samples, which take none)
 };
 
@@ -454,6 +454,7 @@ __device__ __forceinline__ Picked pick(const float (&x)[V], float c, float lo, f
   RoundRange r{c, lo, hi, 0.0f, 8388608.0f + (float)hb, 0u, 3u};
   u32x4* h4 = (u32x4*)cx.hist + l;
   Picked p;
+  p.mask = 0;
   p.tie = lo;
   p.krem = k;
   bool check = !full;
@@ -521,10 +522,17 @@ __device__ __forceinline__ Picked pick(const float (&x)[V], float c, float lo, f
         for (int j = 0; j < V; ++j) Op::template append<true, true>(x[j], r, q);
       }
       p.v = slots_end<V>(q, cx, p.mask);
-      p.lo = r.lo;
-      p.hi = r.hi;
-      p.first = off;
-      p.last = off + r.width;
+      const double step = (double)span * (1.0 / 1020.0);
+      p.t_lo = (double)r.lo + ((double)off - 0.5) * step;
+      p.t_hi = (double)r.lo + ((double)(off + r.width) + 0.5) * step;
+      if (__builtin_expect(iter != 0, 0)) {
+        // keys outside a later round's range were masked off, however near: the
+        // interval ends at the range (as a branch: the usual series, decided by its
+        // first round, pays two instructions)
+        p.t_lo = fmax(p.t_lo, (double)r.lo);
+        p.t_hi = fmin(p.t_hi, (double)r.hi);
+        asm volatile("");
+      }
       p.ok = p.mask != 0;
       if (p.ok) return p;
     }
@@ -550,17 +558,11 @@ __device__ __forceinline__ Picked pick(const float (&x)[V], float c, float lo, f
 // than t_hi - delta (up to the rounding of keys and bounds, within 1 -+ 2^-20),
 // so ranks found among the members are the series' own if the values keep that
 // far inside. delta = 0 needs no check: rounding is monotone.
-// bounds() forms [t_lo, t_hi], after the ranks, when the values that they take are free.
-template <class Bounds>
-__device__ __forceinline__ bool rank_distances(float v, uint64_t mask, int krem, const Bounds& bounds, double med,
+__device__ __forceinline__ bool rank_distances(float v, uint64_t mask, int krem, double t_lo, double t_hi, double med,
                                                bool even, double delta, double& mad) {
   double a, b;
   two_ranks(fabs((double)v - med), mask, krem, even, a, b);
-  if (delta != 0.0) {
-    double t_lo, t_hi;
-    bounds(t_lo, t_hi);
-    if (a < t_lo * (1.0 + 0x1p-20) + delta || b > t_hi * (1.0 - 0x1p-20) - delta) return false;
-  }
+  if (delta != 0.0 && (a < t_lo * (1.0 + 0x1p-20) + delta || b > t_hi * (1.0 - 0x1p-20) - delta)) return false;
   mad = even ? (a + b) * 0.5 : a;
   return true;
 }
@@ -574,16 +576,7 @@ __device__ __forceinline__ bool mad_from_keys(const float (&x)[V], double med, i
   const float dmax = fmaxf(fabsf(xmin - mf), fabsf(xmax - mf));
   const Picked p = pick<V, true>(x, mf, 0.0f, dmax, k, even, full, cx);
   if (!p.ok) return false;
-  auto bounds = [&](double& t_lo, double& t_hi) {
-    const double lo = p.lo, step = (double)(p.hi - p.lo) * (1.0 / 1020.0);
-    t_lo = lo + ((double)p.first - 0.5) * step;
-    t_hi = lo + ((double)p.last + 0.5) * step;
-    if (!p.one) {                                  // keys outside a later round's range were masked off, however near
-      t_lo = fmax(t_lo, lo);
-      t_hi = fmin(t_hi, (double)p.hi);
-    }
-  };
-  if (p.mask) return rank_distances(p.v, p.mask, p.krem, bounds, med, even, delta, mad);
+  if (p.mask) return rank_distances(p.v, p.mask, p.krem, p.t_lo, p.t_hi, med, even, delta, mad);
   if (delta != 0.0) return false;
   // many equal keys: their one FP64 distance, if it is one
   double dlo = __builtin_inf(), dhi = -__builtin_inf();
@@ -665,8 +658,7 @@ __device__ __forceinline__ bool mad_from_bracket(const float (&x)[V], double med
   below = wave_sum(below);
   const int krem = k - below;
   if (!(krem >= 0 && krem + (even ? 1 : 0) < popc64(mask))) return false;
-  auto bounds = [&](double& lo, double& hi) { lo = t_lo; hi = t_hi; };
-  return rank_distances(v, mask, krem, bounds, med, even, delta, mad);
+  return rank_distances(v, mask, krem, t_lo, t_hi, med, even, delta, mad);
 }
 
 // The (rank)-th and (rank+1)-th smallest FP64 values val(j) among the samples
