@@ -675,6 +675,32 @@ extern "C" int nsfrb_debug_plan_source(const nsfrb_search_config* cfg, char* out
 }
 
 // ------------------------------------------------------------------ handle
+// Best maps up to kBestStaged bytes come over in one copy: with 16 x 4 copies of
+// 64 x 64 pixels to pageable memory a batch call took 2.89 ms, with 16 to pinned
+// memory and from there to the caller 2.21. Larger ones are bound by the bus. The
+// cubes of a batch share one buffer; where none can be pinned, maps are copied one
+// by one.
+constexpr size_t kBestStaged = (size_t)4 << 20;
+struct BestStage {
+  void* host = nullptr;
+  size_t bytes = 0;
+  std::mutex mu;                       // guards host
+  ~BestStage() {
+    if (host) hipHostFree(host);
+  }
+};
+static std::shared_ptr<BestStage> best_stage(size_t bytes) {
+  const char* force = std::getenv("NSFRB_FORCE_PIN_FAIL");     // (tests)
+  if (bytes == 0 || (force && std::atoi(force) != 0)) return nullptr;
+  auto s = std::make_shared<BestStage>();
+  if (hipHostMalloc(&s->host, bytes, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  s->bytes = bytes;
+  return s;
+}
+
 struct nsfrb_search {
   nsfrb_search_config cfg{};
   std::vector<double> freqs, dms;
@@ -712,8 +738,7 @@ struct nsfrb_search {
   float* d_best_s = nullptr;
   int32_t *d_best_d = nullptr, *d_best_w = nullptr, *d_best_t = nullptr;
   size_t best_pitch = 0;
-  void* h_best = nullptr;              // pinned copy of them on its way to the caller
-  std::mutex best_mu;                  // guards h_best
+  std::shared_ptr<BestStage> stage;    // where they pass on their way to the caller
   unsigned long long* d_keys = nullptr;
   int32_t* d_count = nullptr;
   unsigned long long* d_flags = nullptr;   // zero between runs
@@ -727,14 +752,16 @@ struct nsfrb_search {
   const void* last_z = nullptr;        // normalised cube searched by the last run
 };
 
-// Best maps up to this many bytes come over in one copy: with 16 x 4 copies of
-// 64 x 64 pixels to pageable memory a batch call took 2.89 ms, with 16 to pinned
-// memory and from there to the caller 2.21. Larger ones are bound by the bus.
-constexpr size_t kBestStaged = (size_t)4 << 20;
 
 template <typename T>
 static hipError_t dalloc(T** p, size_t n) {
   return hipMalloc((void**)p, n * sizeof(T) > 0 ? n * sizeof(T) : 16);
+}
+
+// Bytes of the handle's maps that pass through a BestStage (0: too many).
+static size_t staged_bytes(const nsfrb_search* h) {
+  const size_t bytes = 4 * h->best_pitch * sizeof(float);
+  return bytes <= kBestStaged ? bytes : 0;
 }
 
 static void release(nsfrb_search* h) {
@@ -747,7 +774,6 @@ static void release(nsfrb_search* h) {
   if (h->d_delays_zeroed) hipFree(h->d_delays_zeroed);
   if (h->h_cands) hipHostFree(h->h_cands);
   if (h->h_nout) hipHostFree(h->h_nout);
-  if (h->h_best) hipHostFree(h->h_best);
   if (h->done) hipEventDestroy(h->done);
   for (auto& e : h->ev)
     if (e) hipEventDestroy(e);
@@ -911,8 +937,7 @@ static nsfrb_status search_create(const nsfrb_search_config* cfg, bool plan_now,
   h->d_best_d = (int32_t*)h->d_best_s + h->best_pitch;
   h->d_best_w = h->d_best_d + h->best_pitch;
   h->d_best_t = h->d_best_w + h->best_pitch;
-  if (const size_t bytes = 4 * h->best_pitch * sizeof(float); bytes <= kBestStaged)
-    HIP_TRY(hipHostMalloc(&h->h_best, bytes, hipHostMallocDefault));
+  if (plan_now) h->stage = best_stage(staged_bytes(h.get()));
   HIP_TRY(dalloc(&h->d_keys, std::max(n_pix, (size_t)cand_counters())));
   HIP_TRY(dalloc(&h->d_count, (size_t)cand_counters()));
   HIP_TRY(dalloc(&h->d_flags, 1));
@@ -1240,10 +1265,10 @@ extern "C" nsfrb_status nsfrb_best_get(nsfrb_search* h, float* snr, int32_t* dm_
   nsfrb_status st = wait_run(h);
   if (st != NSFRB_OK) return st;
   const size_t n = (size_t)h->n_pix;
-  if (snr && dm_index && width_index && toa && h->h_best) {
-    std::lock_guard<std::mutex> lk(h->best_mu);
-    HIP_TRY(hipMemcpy(h->h_best, h->d_best_s, 4 * h->best_pitch * sizeof(float), hipMemcpyDeviceToHost));
-    const float* p = (const float*)h->h_best;
+  if (snr && dm_index && width_index && toa && h->stage && staged_bytes(h)) {
+    std::lock_guard<std::mutex> lk(h->stage->mu);
+    HIP_TRY(hipMemcpy(h->stage->host, h->d_best_s, staged_bytes(h), hipMemcpyDeviceToHost));
+    const float* p = (const float*)h->stage->host;
     std::memcpy(snr, p, n * sizeof(float));
     std::memcpy(dm_index, p + h->best_pitch, n * sizeof(int32_t));
     std::memcpy(width_index, p + 2 * h->best_pitch, n * sizeof(int32_t));
@@ -1503,6 +1528,10 @@ extern "C" nsfrb_status nsfrb_batch_create(const nsfrb_search_config* cfgs, int3
     if (st != NSFRB_OK) return fail(st, "cube " + std::to_string(i) + ": " + g_last_error);
     b->cubes.push_back(h);
   }
+  size_t staged = 0;
+  for (const nsfrb_search* h : b->cubes) staged = std::max(staged, staged_bytes(h));
+  const std::shared_ptr<BestStage> stage = best_stage(staged);
+  for (nsfrb_search* h : b->cubes) h->stage = stage;
   // one module with a persistent kernel per class; like a single cube's plan it
   // is regenerated lean, then with fewer accumulators per pass, while a class
   // kernel would spill more than a search kernel may, and refused only after

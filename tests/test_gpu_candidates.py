@@ -111,3 +111,23 @@ def test_runs_after_overlapping_ones():
             s.run(x.data_ptr(), streams[0].cuda_stream)
             assert got(s) == expected(want, -50.0, 16, 256)
             assert s.flag_count() == flagged.size
+
+
+@pytest.mark.parametrize("pinned", [True, False])
+def test_best_maps_through_shared_or_no_pinned_memory(monkeypatch, pinned):
+    """Cubes of one batch share a pinned buffer; maps too large for it, or all where none can be pinned, are copied singly."""
+    if not pinned:
+        monkeypatch.setenv("NSFRB_FORCE_PIN_FAIL", "1")
+    rng = np.random.default_rng(4)
+    shapes = [(5, 3), (520, 510), (512, 512), (64, 64)]
+    vs = [values("distinct", nx * ny, rng) for nx, ny in shapes]
+    xs = [torch.from_numpy(v).cuda() for v in vs]
+    with nsfrb.Batch([config(nx, ny, 4, 1e9) for nx, ny in shapes]) as b:
+        b.run([x.data_ptr() for x in xs])
+        for i in (3, 0, 2, 1):
+            snr, d, w, t = b.best(i)
+            np.testing.assert_array_equal(np.asarray(snr).ravel(), vs[i])
+            assert not np.any(d) and not np.any(w) and not np.any(t)
+    with nsfrb.Search(config(64, 64, 4, 1e9)) as s:
+        s.run(xs[3].data_ptr())
+        np.testing.assert_array_equal(np.asarray(s.best()[0]).ravel(), vs[3])
