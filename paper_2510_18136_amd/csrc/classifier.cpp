@@ -61,8 +61,8 @@ struct nsfrb_classifier {
   uint16_t* d_wb[4] = {};      // BF16 backward-data weights (flipped taps, transposed channels; layers 2..4)
   uint16_t* d_act[4] = {};     // conv outputs a_1..a_4 [n][t][y][x][32]
   uint16_t* d_dpre[4] = {};    // pre-activation gradients of conv layers 1..4 (kept for inspection; flagged rows only)
-  uint8_t* d_nz[4] = {};       // their row flags [n][t * y]: unflagged rows are zero and not stored
   uint32_t* d_bad = nullptr;   // samples with a non-finite pre-activation
+  uint8_t* d_nz[4] = {};       // row flags of d_dpre [n][t * y]: unflagged rows are zero and not stored (behind d_bad)
   float* d_part = nullptr;
   float* d_part_db = nullptr;
   float* d_h = nullptr;         // head input [n][64]: channel maxima, candidate-position features
@@ -99,8 +99,6 @@ void release(nsfrb_classifier* c) {
     if (c->d_act[l]) hipFree(c->d_act[l]);
   }
   for (auto* p : c->d_dpre)
-    if (p) hipFree(p);
-  for (auto* p : c->d_nz)
     if (p) hipFree(p);
   if (c->h_loss) hipHostFree(c->h_loss);
   delete c;
@@ -167,12 +165,11 @@ extern "C" nsfrb_status nsfrb_classifier_create(const nsfrb_classifier_config* c
     NSFRB_HIP_TRY(dalloc(&c->d_act[l], N * npos * kCh));
   }
   for (auto& p : c->d_dpre) NSFRB_HIP_TRY(dalloc(&p, N * npos * kCh));
-  for (auto& p : c->d_nz) {
-    NSFRB_HIP_TRY(dalloc(&p, N * npos / kX));
-    NSFRB_HIP_TRY(hipMemset(p, 0, N * npos / kX));
-  }
-  NSFRB_HIP_TRY(dalloc(&c->d_bad, N));
-  NSFRB_HIP_TRY(hipMemset(c->d_bad, 0, N * sizeof(uint32_t)));
+  // the flags of all layers in one allocation, behind the samples'
+  const size_t rows = N * npos / kX, flag_bytes = N * sizeof(uint32_t) + 4 * rows;
+  NSFRB_HIP_TRY(hipMalloc((void**)&c->d_bad, flag_bytes));
+  NSFRB_HIP_TRY(hipMemset(c->d_bad, 0, flag_bytes));
+  for (int l = 0; l < 4; ++l) c->d_nz[l] = (uint8_t*)(c->d_bad + N) + l * rows;
   const size_t items = (size_t)wgrad_items((int)N, cfg->ny);
   NSFRB_HIP_TRY(dalloc(&c->d_part, items * kTap * kCh * kCh));
   NSFRB_HIP_TRY(dalloc(&c->d_part_db, items * kCh));
