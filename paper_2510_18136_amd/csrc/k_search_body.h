@@ -252,7 +252,7 @@ __device__ __forceinline__ void reads_first() { __builtin_amdgcn_sched_barrier(0
 // survey quarter), as do lean plans (NSFRB_LEAN: the tuned one would spill); they
 // leave the order of reads and adds to the compiler. delay(s): sub-band s's delay,
 // a uniform value.
-constexpr int kSplitC = 20;
+constexpr int kSplitC = NSFRB_SPLIT_C;   // fixed by the plan, whose generated parts of a row depend on it
 constexpr bool split_rows(int C) { return C >= kSplitC && !NSFRB_LEAN; }
 template <int C, typename T, class Delay>
 __device__ __forceinline__ void dedisperse(float (&cur)[C], const T* rows, int rs, int n_sub, const Delay& delay, int l) {
@@ -694,11 +694,13 @@ __device__ __forceinline__ void stage_rows_w(const CubeDesc& cd, int p, ST* buf,
   else if constexpr (sizeof(ST) == 2) stage_rows_par<NW>(cd, p, buf, wv, l);
 }
 
-// Between requesting a pixel's rows and waiting for them, a wave issues no
-// vector-memory load (the class table comes through the scalar cache, the S/N
-// normalisers are read once per kernel, trial validity comes from the table):
-// on gfx950 one counter tracks all vector-memory loads, so any load there
-// would wait for the row requests too.
+// Between requesting a pixel's rows and waiting for them, a wave issues as few
+// vector-memory loads as it can (the class table comes through the scalar cache,
+// the S/N normalisers are read once per kernel, trial validity comes from the
+// table): on gfx950 one counter tracks all vector-memory loads, so a load there
+// waits for the row requests too. With two LDS buffers and more than 2 NW trials,
+// rows read in halves do load the delays of a later round there, two rounds ahead
+// of their use.
 // ---------------------------------------------------------------------------
 // Persistent form of search_group for one pixel per workgroup: the workgroup
 // walks pixels b, b + G, ... (workgroup b of G); its NW waves split the
@@ -706,9 +708,8 @@ __device__ __forceinline__ void stage_rows_w(const CubeDesc& cd, int p, ST* buf,
 // the next pixel are requested with global-to-LDS loads as soon as no wave will
 // read the current rows again (after the last round's de-dispersion; with two
 // LDS buffers, at the start of the pixel), so those loads run under the boxcar
-// work. Delays and DM bounds come through the scalar cache and the S/N
-// normalisers are read once, so no vector-memory load is issued while row
-// requests are in flight (one counter tracks them all).
+// work. DM bounds come through the scalar cache and the S/N normalisers are read
+// once; for the delays see search_pixel_dms.
 // ---------------------------------------------------------------------------
 // A load through the scalar cache (the constant address space): for values the
 // kernel never writes, at uniform addresses.
@@ -856,9 +857,7 @@ __device__ __forceinline__ ItemWalk xcd_walk(long long n) {
 // Persistent single-cube form: one pixel per workgroup at a time; the next
 // pixel's rows (global-to-LDS, 16-byte lanes) are requested as soon as no
 // wave reads the current ones (after the last round's de-dispersion; with two
-// LDS buffers, at the start of the pixel). No vector-memory load is issued
-// while row requests are in flight (one counter tracks them all): delays and
-// DM bounds come through the scalar cache, the S/N normalisers are read once.
+// LDS buffers, at the start of the pixel).
 template <int LC, int NW, int NBUF>
 __device__ __forceinline__ void search_persistent(const CubeDesc& cd, const int* __restrict__ delays,
                                                   const int* __restrict__ dmaxv) {

@@ -321,7 +321,7 @@ static nsfrb_status gen_chain(const std::vector<int>& widths, std::string& out, 
 // maximum tree they saved 4% of the instructions of a survey trial, but width
 // lists that already fill the registers spilled. %0 result, %1 scratch, %2 M,
 // %3 L, then the registers b[0..C).
-static constexpr int kSplitC = 20;         // samples per lane from which rows are read in two parts, as in k_search_body.h
+static constexpr int kSplitC = 20;         // samples per lane from which rows are read in two parts (k_search_body.h)
 static constexpr int kArgGroup = 5;
 static constexpr int kArgGroupedC = 17;    // fewer samples per lane keep one compare per register
 static std::string gen_locate(int C) {
@@ -427,6 +427,7 @@ static std::string gen_source(int store, int nw, int npass, const std::string& c
   std::ostringstream o;
   o << "#define NSFRB_RTC_PROLOGUE 1\n#include \"device_common.h\"\n";
   o << "#define NSFRB_LEAN " << lean << "\n";
+  o << "#define NSFRB_SPLIT_C " << kSplitC << "\n";
   o << "#define NSFRB_NPASS " << npass << "\n";
   o << "typedef " << store_type_name(store) << " ST;\n";
   o << "#define NSFRB_NW " << nw << "\n";
@@ -1417,10 +1418,14 @@ static void batch_release(nsfrb_batch* b) {
 // Pixels per batch work item (tile: one pixel's LDS rows in bytes): two for
 // short series (C <= 18 samples per lane), whose items are short enough that
 // the per-item wait for rows and the barriers show; one otherwise, where a
-// second pixel's tile would cost a workgroup per CU. Measured per class on the
-// 64-cube benchmark batch: two pixels saved 4-10% on C = 6..18 and cost
-// 28-50% on C = 22..30. NSFRB_BATCH_PIX = 1, 2 or 4 sets the count (studies);
-// never more than fit in LDS.
+// second pixel's tile would cost a workgroup per CU. Six cubes of 64 x 64 x 16,
+// five widths, one against two pixels: FP16, 8 trials (8 waves), 300 samples 0.38
+// against 0.35 ms, 800 0.48 against 0.44, 1100 0.60 against 0.57, 1300 0.63 against
+// 0.91; 16 trials (16 waves) 0.77 against 0.65 at 300, 1.02 against 0.93 at 1100;
+// FP32, 16 trials 0.58 against 0.46 at 300, 0.92 against 0.82 at 1100. FP32 with 8
+// waves gains to 300 samples (0.28 against 0.26) and loses from 600 on (0.39
+// against 0.57): the line does not part the store types yet. NSFRB_BATCH_PIX = 1, 2
+// or 4 sets the count (studies); never more than fit in LDS.
 static int batch_pixels_per_item(int C, int nw, int env, size_t tile) {
   int pix = (env == 1 || env == 2 || env == 4) ? env : (C <= 18 ? 2 : 1);
   pix = std::min(pix, nw);
