@@ -176,19 +176,17 @@ __device__ __forceinline__ void cand_top(const CandDesc& d, int blk, TopShared& 
     n = block_sum(n, sh);
     __syncthreads();
     const uint32_t Tm = n > K ? kth_largest<PM>(k32, K, sh) : 1u;
-    uint32_t Tp = 0;                                          // of keys equal to Tm, the low words from here on
-    for (;;) {
-      if (tid == 0) fill = 0;
-      __syncthreads();
+    if (tid == 0) fill = 0;
+    __syncthreads();
 #pragma unroll
-      for (int i = 0; i < PM; ++i)
-        if (k32[i] > Tm || (k32[i] == Tm && (uint32_t)k64[i] >= Tp)) {
-          const int at = atomicAdd(&fill, 1);
-          if (at < kTopMaxK) s[at] = k64[i];
-        }
-      __syncthreads();
-      n = fill;                                               // K, or more if the K-th is tied
-      if (n <= kTopMaxK || Tp) break;                         // uniform
+    for (int i = 0; i < PM; ++i)
+      if (k32[i] >= Tm) {
+        const int at = atomicAdd(&fill, 1);
+        if (at < kTopMaxK) s[at] = k64[i];
+      }
+    __syncthreads();
+    n = fill;                                                 // K, or more if the K-th is tied
+    if (__builtin_expect(n > kTopMaxK, 0)) {
       // too many ties to rank: only those of the smallest pixels, whose low words
       // are the largest (4,096 equal keys ranked took 0.89 ms, so 0.04)
       int above = 0;
@@ -200,7 +198,17 @@ __device__ __forceinline__ void cand_top(const CandDesc& d, int blk, TopShared& 
       }
       above = block_sum(above, sh);
       __syncthreads();
-      Tp = max(1u, kth_largest<PM>(low, K - above, sh));
+      const uint32_t Tp = max(1u, kth_largest<PM>(low, K - above, sh));
+      if (tid == 0) fill = 0;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < PM; ++i)
+        if (k32[i] > Tm || low[i] >= Tp) {
+          const int at = atomicAdd(&fill, 1);
+          if (at < kTopMaxK) s[at] = k64[i];
+        }
+      __syncthreads();
+      n = fill;
     }
     n = min(n, kTopMaxK);                                     // (more only if runs overlap)
   }
