@@ -684,7 +684,6 @@ extern "C" int nsfrb_debug_plan_source(const nsfrb_search_config* cfg, char* out
 constexpr size_t kBestStaged = (size_t)4 << 20;
 struct BestStage {
   void* host = nullptr;
-  size_t bytes = 0;
   std::mutex mu;                       // guards host
   ~BestStage() {
     if (host) hipHostFree(host);
@@ -698,7 +697,6 @@ static std::shared_ptr<BestStage> best_stage(size_t bytes) {
     (void)hipGetLastError();
     return nullptr;
   }
-  s->bytes = bytes;
   return s;
 }
 
@@ -752,7 +750,6 @@ struct nsfrb_search {
   bool profiling = false, ran = false, ext_set = false;
   const void* last_z = nullptr;        // normalised cube searched by the last run
 };
-
 
 template <typename T>
 static hipError_t dalloc(T** p, size_t n) {
