@@ -244,9 +244,11 @@ __device__ __forceinline__ void reads_first() { __builtin_amdgcn_sched_barrier(0
 
 // De-dispersion by row reads that are grouped ahead of their adds: series of
 // kSplitC samples per lane or more are read in two half rows, the other half in
-// flight while one is added (sub-band s's delay in lane s of dlv; with the delay
-// behind a function this loop too held a second row: 35 samples, FP32, five
-// widths, 16 waves: 52 bytes of spill against 0). Shorter ones run with enough
+// flight while one is added. Odd counts take the register that holds sub-band s's
+// delay in lane s: with the delay behind a function this loop too held a second row
+// (35 samples, FP32, five widths, 16 waves: 52 bytes of spill against 0). Even
+// counts take the function, which schedules better there (FP32 survey call 13.44
+// against 13.54 ms). Shorter ones run with enough
 // waves to hide the read latency, and lose more by the registers (waves) the
 // second half costs (7 samples per lane: 517 against 582 us for a 5x-binned
 // survey quarter), as do lean plans (NSFRB_LEAN: the tuned one would spill); they
@@ -265,15 +267,17 @@ __device__ __forceinline__ void dedisperse(float (&cur)[C], const T* rows, int r
     a.add(cur, dl);
   }
 }
-template <int C, typename T>
-__device__ __forceinline__ void dedisperse_split(float (&cur)[C], const T* rows, int rs, int n_sub, int dlv, int l) {
+__device__ __forceinline__ int delay_of(int dlv, int s) { return __builtin_amdgcn_readlane(dlv, s); }
+template <class Delay> __device__ __forceinline__ int delay_of(const Delay& delay, int s) { return delay(s); }
+template <int C, typename T, class Delay>
+__device__ __forceinline__ void dedisperse_split(float (&cur)[C], const T* rows, int rs, int n_sub, const Delay& delay, int l) {
 #pragma unroll
   for (int c = 0; c < C; ++c) cur[c] = 0.f;
   constexpr bool paired = (C & 1) == 0;
   constexpr int H = (C / 2 + 1) & ~1;                  // even, about half a row
   RowPart<T, H, paired> a;
   RowPart<T, C - H, paired> b;
-  int dl = __builtin_amdgcn_readlane(dlv, 0);
+  int dl = delay_of(delay, 0);
   a.template load<C, 0>(rows, dl, l);
   for (int s = 0; s < n_sub; ++s) {
     b.template load<C, H>(rows + s * rs, dl, l);
@@ -282,7 +286,7 @@ __device__ __forceinline__ void dedisperse_split(float (&cur)[C], const T* rows,
     // (the last row's first half is read once more: a branch around the reads
     // would make the compiler copy the registers)
     const int sn = s + 1 < n_sub ? s + 1 : s;
-    const int dn = __builtin_amdgcn_readlane(dlv, sn);
+    const int dn = delay_of(delay, sn);
     reads_first();
     a.template load<C, 0>(rows + sn * rs, dn, l);
     reads_first();
@@ -559,8 +563,10 @@ __device__ __forceinline__ void search_group(const CubeDesc& cd, int p0, ST* zl,
       }
       for (int pass = 0; pass < NSFRB_NPASS; ++pass) {
         float cur[C];
-        if constexpr (split_rows(C)) {
+        if constexpr (split_rows(C) && (C & 1)) {
           dedisperse_split<C>(cur, zbase, rs, n_sub, dl_cur, l);
+        } else if constexpr (split_rows(C)) {
+          dedisperse_split<C>(cur, zbase, rs, n_sub, [&](int s) { return __builtin_amdgcn_readlane(dl_cur, s); }, l);
         } else if constexpr (NSFRB_LEAN == 2) {
 #pragma unroll
           for (int c = 0; c < C; ++c) cur[c] = 0.f;
@@ -772,8 +778,10 @@ __device__ __forceinline__ void search_pixel_dms(const CubeDesc& cd, const int* 
     }
     for (int pass = 0; pass < NSFRB_NPASS; ++pass) {
       float cur[C];
-      if constexpr (split_rows(C)) {
+      if constexpr (split_rows(C) && (C & 1)) {
         dedisperse_split<C>(cur, zl, rs, n_sub, dlv, l);
+      } else if constexpr (split_rows(C)) {
+        dedisperse_split<C>(cur, zl, rs, n_sub, [&](int s) { return __builtin_amdgcn_readlane(dlv, s); }, l);
       } else if constexpr (NSFRB_LEAN == 2) {    // (PAR: rows placed at their parity offset, see stage_rows_par)
 #pragma unroll
         for (int c = 0; c < C; ++c) cur[c] = 0.f;
